@@ -76,33 +76,14 @@ struct DevEvent {
     const float *track_par;              // [n_tracks][6]
     const float *track_cov;              // [n_tracks][21]
     const int *track_hits;               // [n_tracks][n_layers]
-    // build outputs
-    double *out_par;                     // [n_seeds][6]
-    double *out_cov;                     // [n_seeds][21]
+    // results, FP32: one record of kRecWords words per row (see below), widened to FP64 on their way out
+    float *out_rec;                      // [n_seeds] build
     int *out_hits;                       // [n_seeds][n_layers]
-    int *out_nhits;
-    int *out_nholes;
-    double *out_chi2;
-    int *out_status;
-    // fit outputs
-    double *fit_par;                     // [n_tracks][6]
-    double *fit_cov;                     // [n_tracks][21]
-    double *fit_chi2;
-    int *fit_nupd;
-    int *fit_status;
-    double *rf_par;                      // [n_seeds][6] final fit of the built tracks
-    double *rf_cov;                      // [n_seeds][21]
-    double *rf_chi2;                     // [n_seeds]
-    int *rf_nupd;                        // [n_seeds]
-    int *rf_status;                      // [n_seeds]
+    float *fit_rec;                      // [n_tracks] fit
+    float *rf_rec;                       // [n_seeds] final fit of the built tracks
     // the whole final beam (set only for a build that asks for it; null otherwise)
-    double *beam_par;                    // [n_seeds * max_cands][6]
-    double *beam_cov;                    // [n_seeds * max_cands][21]
+    float *beam_rec;                     // [n_seeds * max_cands]
     int *beam_hits;                      // [n_seeds * max_cands][n_layers]
-    int *beam_nhits;
-    int *beam_nholes;
-    double *beam_chi2;
-    int *beam_status;                    // -1: no candidate at that rank
     unsigned long long *stats;           // [5] mkf_build_stats counters
     // plain per-layer builder state (slots = n_seeds * lanes_per_seed)
     float *st_par;                       // [6][slots]
@@ -113,6 +94,41 @@ struct DevEvent {
     int *st_hist;                        // [n_layers][slots] parent rank << 24 | hit (0xFFFFFF: hole)
     int st_slots;
     int grid_k;                          // the event's bin grid: (bins_phi >> grid_k) x (bins_z >> grid_k)
+};
+
+// A result row on the device: the state (6 words), the packed covariance
+// (21), then the words named here; the counts and the status are integer
+// bits.  32 words are one 128-byte cache line, so that a row written by one
+// lane in an arbitrary order of rows (the batched builder takes the seeds in
+// azimuth order) leaves the L2 as a whole line, and rows are half the size of
+// the FP64 arrays the caller gets.
+constexpr int kRecWords = 32;
+enum : int {
+    kRecCov = 6,
+    kRecChi2 = 27,
+    kRecHits = 28,      // hits on the track / updates of a fit
+    kRecHoles = 29,
+    kRecStatus = 30,    // -1: no candidate at that rank of the beam
+};
+
+// Result rows on their way to the caller's arrays (k_deliver): n rows from
+// `rec` and `hits`, the arrays in memory the device can write (page-locked
+// host memory), any of them null when not wanted.
+struct DeliverJob {
+    const float *rec;
+    const int *hits;         // [n][n_layers]
+    double *par, *cov, *chi2;
+    int *hits_out, *n_hits, *n_holes, *ndof, *status;
+    int n;
+    int first_tile;          // tiles of the launch before this job's
+};
+constexpr int kDeliverTile = kWave;   // rows a wavefront moves at a time
+constexpr int kDeliverJobs = 32;      // jobs of one launch (they travel in its arguments)
+struct DeliverArgs {
+    DeliverJob job[kDeliverJobs];
+    int n_jobs;
+    int n_tiles;
+    int n_layers;
 };
 
 // A batch: events plus the flattened work decomposition over them.
@@ -176,6 +192,7 @@ hipError_t launch_build_layer(const Params &p, const DevEvent *ev_dev, const Dev
                               int lanes_per_seed, int waves_per_block, bool stats, hipStream_t s);
 hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s);
 hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s);
+hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s);
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 hipError_t launch_calib_fma(float *dst, int n_blocks, int iters, hipStream_t s);   // iters: multiple of 4
 int calib_fma_chains();

@@ -141,23 +141,10 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     v->binned = c.take<float4>(n);
     v->bin_of = c.take<int>(n);
     v->bin_rank = c.take<int>(n);
-    v->out_par = c.take<double>(6 * ns);
-    v->out_cov = c.take<double>(21 * ns);
+    v->out_rec = c.take<float>(kRecWords * ns);
     v->out_hits = c.take<int>(nl * ns);
-    v->out_nhits = c.take<int>(ns);
-    v->out_nholes = c.take<int>(ns);
-    v->out_chi2 = c.take<double>(ns);
-    v->out_status = c.take<int>(ns);
-    v->fit_par = c.take<double>(6 * nt);
-    v->fit_cov = c.take<double>(21 * nt);
-    v->fit_chi2 = c.take<double>(nt);
-    v->fit_nupd = c.take<int>(nt);
-    v->fit_status = c.take<int>(nt);
-    v->rf_par = c.take<double>(6 * ns);
-    v->rf_cov = c.take<double>(21 * ns);
-    v->rf_chi2 = c.take<double>(ns);
-    v->rf_nupd = c.take<int>(ns);
-    v->rf_status = c.take<int>(ns);
+    v->fit_rec = c.take<float>(kRecWords * nt);
+    v->rf_rec = c.take<float>(kRecWords * ns);
     v->stats = c.take<unsigned long long>(5);
     DevEvent *dv = c.take<DevEvent>(1);
     if (dev_view) *dev_view = dv;
@@ -795,13 +782,8 @@ mkf_status ensure_beam(mkf_ctx *ctx, EventRec *rec)
     auto carve = [&](void *base) {
         Carver c(base);
         DevEvent &v = rec->beam_view;
-        v.beam_par = c.take<double>(6 * n);
-        v.beam_cov = c.take<double>(21 * n);
-        v.beam_chi2 = c.take<double>(n);
+        v.beam_rec = c.take<float>(kRecWords * n);
         v.beam_hits = c.take<int>(nl * n);
-        v.beam_nhits = c.take<int>(n);
-        v.beam_nholes = c.take<int>(n);
-        v.beam_status = c.take<int>(n);
         return c.off;
     };
     const size_t bytes = carve(nullptr);
@@ -892,13 +874,8 @@ mkf_status compose_batch(EventRec *const *recs, int n, int spi, bool beam, char 
         ev[i] = recs[i]->view;
         if (beam) {   // this launch also writes every rank of the final beam
             const DevEvent &b = recs[i]->beam_view;
-            ev[i].beam_par = b.beam_par;
-            ev[i].beam_cov = b.beam_cov;
+            ev[i].beam_rec = b.beam_rec;
             ev[i].beam_hits = b.beam_hits;
-            ev[i].beam_nhits = b.beam_nhits;
-            ev[i].beam_nholes = b.beam_nholes;
-            ev[i].beam_chi2 = b.beam_chi2;
-            ev[i].beam_status = b.beam_status;
         }
         ip[i] = (int)items;
         hp[i] = (int)hits;
@@ -993,38 +970,244 @@ mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t,
     return MKF_OK;
 }
 
-static mkf_status copy_d2h(void *dst, const void *src, size_t bytes, hipStream_t s)
+size_t field_bytes(int f, int n_layers)
 {
-    if (!dst || bytes == 0) return MKF_OK;
-    MKF_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
-    return MKF_OK;
+    const size_t b[kOutFields] = {48, 168, 8, 4 * (size_t)n_layers, 4, 4, 4, 4};
+    return b[f];
 }
 
-mkf_status copy_tracks_out(mkf_ctx *ctx, const EventRec *rec, const mkf_tracks *out, hipStream_t s)
+void *field_of(const mkf_tracks &t, int f)
 {
-    (void)ctx;
-    const DevEvent &v = rec->view;
-    const size_t n = (size_t)rec->shape.n_seeds, nl = (size_t)rec->shape.n_layers;
-    mkf_status st;
-    if ((st = copy_d2h(out->par, v.out_par, 48 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->cov, v.out_cov, 168 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->hits, v.out_hits, 4 * nl * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->n_hits, v.out_nhits, 4 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->n_holes, v.out_nholes, 4 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->chi2, v.out_chi2, 8 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->status, v.out_status, 4 * n, s)) != MKF_OK) return st;
-    if (out->ndof) {
-        // 2 measured coordinates per hit, minus the 5 track parameters
-        if ((st = copy_d2h(out->ndof, v.out_nhits, 4 * n, s)) != MKF_OK) return st;
+    void *const p[kOutFields] = {t.par, t.cov, t.chi2, t.hits, t.n_hits, t.n_holes, t.ndof, t.status};
+    return p[f];
+}
+
+void set_field(DeliverJob &j, int f, void *p)
+{
+    switch (f) {
+    case 0: j.par = static_cast<double *>(p); break;
+    case 1: j.cov = static_cast<double *>(p); break;
+    case 2: j.chi2 = static_cast<double *>(p); break;
+    case 3: j.hits_out = static_cast<int *>(p); break;
+    case 4: j.n_hits = static_cast<int *>(p); break;
+    case 5: j.n_holes = static_cast<int *>(p); break;
+    case 6: j.ndof = static_cast<int *>(p); break;
+    default: j.status = static_cast<int *>(p); break;
     }
+}
+
+void *device_writable(void *p, size_t bytes, size_t align, int device)
+{
+    if (reinterpret_cast<uintptr_t>(p) % align) return nullptr;
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (!a.devicePointer || !(a.type == hipMemoryTypeHost || (a.type == hipMemoryTypeDevice && a.device == device)))
+        return nullptr;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, a.devicePointer) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const size_t off = static_cast<char *>(a.devicePointer) - static_cast<char *>(base);
+    return off <= size && bytes <= size - off ? a.devicePointer : nullptr;
+}
+
+// Page-locked staging of at least `bytes` (contents undefined when it grows).
+static mkf_status ensure_pin(mkf_ctx *ctx, size_t bytes)
+{
+    if (ctx->load_pin_bytes >= bytes) return MKF_OK;
+    MKF_HIP(hipStreamSynchronize(ctx->stream));   // a queued copy may still read it
+    if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
+    ctx->load_pin = nullptr;
+    ctx->load_pin_bytes = 0;
+    MKF_HIP(hipHostMalloc(&ctx->load_pin, bytes, hipHostMallocDefault));
+    ctx->load_pin_bytes = bytes;
     return MKF_OK;
 }
 
-static void finish_ndof(const mkf_tracks *out)
+// Staging that lets `rows` result rows leave without another allocation.
+static size_t out_pin_bytes(size_t rows, int n_layers)
 {
-    if (!out || !out->ndof) return;
-    for (int i = 0; i < out->n; ++i) out->ndof[i] = 2 * out->ndof[i] - 5;
+    size_t row = 0;
+    for (int f = 0; f < kOutFields; ++f) row += field_bytes(f, n_layers);
+    return std::min(kOutSlots * kOutSlotMax, row * rows + kOutSlots * 256 * kOutFields);
 }
+
+namespace {
+
+// Result rows to the caller's arrays by launches of k_deliver on the
+// context's stream.  add() everything, then finish(), which waits for the
+// stream.  The staging is copied from by one thread: waking the packing
+// threads for it took longer than they saved (event of 7,001 tracks 423 us
+// with 8 threads, 389 with one; fitted tracks of 8 x 5,000: 1,023 and 809).
+class Delivery {
+  public:
+    explicit Delivery(mkf_ctx *ctx) : ctx_(ctx)
+    {
+        args_.n_jobs = args_.n_tiles = 0;
+        args_.n_layers = ctx->cfg.n_layers;
+    }
+    // an early return leaves no launch pending that writes the caller's arrays
+    ~Delivery()
+    {
+        if (!finished_) (void)hipStreamSynchronize(ctx_->stream);
+    }
+
+    void add(const OutRows &o)
+    {
+        if (o.n <= 0) return;
+        Rows r{o, {}, 0};
+        bool any = false;
+        const int nl = args_.n_layers;
+        for (int f = 0; f < kOutFields; ++f) {
+            void *p = field_of(o.out, f);
+            if (!p) continue;
+            any = true;
+            r.direct[f] = device_writable(p, field_bytes(f, nl) * o.n, f < kOutDoubles ? 8 : 4, ctx_->device);
+            if (!r.direct[f]) r.staged += field_bytes(f, nl);
+        }
+        if (!any) return;
+        staged_ += r.staged * o.n;
+        rows_.push_back(r);
+    }
+
+    mkf_status finish()
+    {
+        mkf_status st;
+        if (staged_) {
+            const size_t pad = 256 * kOutFields * (rows_.size() + kOutSlots);
+            const size_t want = (staged_ + pad + kOutSlots - 1) / kOutSlots;
+            slot_bytes_ = (std::min(std::max(want, kOutSlotMin), kOutSlotMax) + 255) & ~size_t(255);
+            if ((st = ensure_pin(ctx_, std::min(staged_ + pad, kOutSlots * slot_bytes_))) != MKF_OK) return st;
+            slot_bytes_ = std::min(slot_bytes_, ctx_->load_pin_bytes);
+            n_slots_ = (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
+            for (int k = 0; k < n_slots_; ++k)
+                if (!ctx_->out_done[k]) MKF_HIP(hipEventCreateWithFlags(&ctx_->out_done[k], hipEventDisableTiming));
+        }
+        for (const Rows &r : rows_)
+            if ((st = place(r)) != MKF_OK) return st;
+        if ((st = launch()) != MKF_OK) return st;
+        for (int k = 1; k <= n_slots_; ++k)   // oldest first
+            if ((st = empty(slot_[(cur_ + k) % n_slots_])) != MKF_OK) return st;
+        MKF_HIP(hipStreamSynchronize(ctx_->stream));
+        finished_ = true;
+        return MKF_OK;
+    }
+
+  private:
+    struct Rows {
+        OutRows o;
+        void *direct[kOutFields];
+        size_t staged;                  // bytes per row that go through the staging
+    };
+    struct Slot {
+        std::vector<HostCopy> copies;   // not yet made
+        hipEvent_t done = nullptr;
+    };
+
+    // jobs for the rows of r: all at once, or as many as a slot still holds
+    mkf_status place(const Rows &r)
+    {
+        const int nl = args_.n_layers;
+        for (int r0 = 0; r0 < r.o.n;) {
+            int m = r.o.n - r0;
+            mkf_status st;
+            if (r.staged) {
+                const size_t pad = 256 * kOutFields;
+                const size_t least = r.staged * std::min(m, kDeliverTile) + pad;
+                if ((cur_ < 0 || used_ + least > slot_bytes_) && (st = next_slot()) != MKF_OK) return st;
+                m = (int)std::min<size_t>(m, (slot_bytes_ - used_ - pad) / r.staged);
+            }
+            if (args_.n_jobs == kDeliverJobs && (st = launch()) != MKF_OK) return st;
+            DeliverJob &j = args_.job[args_.n_jobs++];
+            j = DeliverJob{};
+            j.rec = r.o.rec + (size_t)kRecWords * r0;
+            j.hits = r.o.hits + (size_t)nl * r0;
+            j.n = m;
+            j.first_tile = args_.n_tiles;
+            args_.n_tiles += (m + kDeliverTile - 1) / kDeliverTile;
+            for (int f = 0; f < kOutFields; ++f) {
+                char *p = static_cast<char *>(field_of(r.o.out, f));
+                if (!p) continue;
+                const size_t fb = field_bytes(f, nl);
+                if (r.direct[f]) {
+                    set_field(j, f, static_cast<char *>(r.direct[f]) + fb * r0);
+                } else {
+                    char *stage = static_cast<char *>(ctx_->load_pin) + cur_ * slot_bytes_ + used_;
+                    used_ += (fb * m + 255) & ~size_t(255);
+                    set_field(j, f, stage);
+                    slot_[cur_].copies.push_back(HostCopy{p + fb * r0, stage, fb * m});
+                }
+            }
+            r0 += m;
+        }
+        return MKF_OK;
+    }
+
+    mkf_status launch()
+    {
+        if (args_.n_jobs == 0) return MKF_OK;
+        MKF_HIP(launch_deliver(args_, ctx_->stream));
+        args_.n_jobs = args_.n_tiles = 0;
+        if (cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
+        return MKF_OK;
+    }
+
+    mkf_status next_slot()
+    {
+        mkf_status st = launch();   // ends the current slot's part
+        if (st != MKF_OK) return st;
+        cur_ = (cur_ + 1) % n_slots_;
+        used_ = 0;
+        slot_[cur_].done = ctx_->out_done[cur_];
+        return empty(slot_[cur_]);
+    }
+
+    // waits until the device has filled the slot and copies its contents out
+    mkf_status empty(Slot &sl)
+    {
+        if (sl.copies.empty()) return MKF_OK;
+        MKF_HIP(hipEventSynchronize(sl.done));
+        for (const HostCopy &c : sl.copies) std::memcpy(c.dst, c.src, c.bytes);
+        sl.copies.clear();
+        return MKF_OK;
+    }
+
+    mkf_ctx *ctx_;
+    DeliverArgs args_;
+    std::vector<Rows> rows_;
+    size_t staged_ = 0, slot_bytes_ = 0, used_ = 0;
+    Slot slot_[kOutSlots];
+    int cur_ = -1, n_slots_ = 0;
+    bool finished_ = false;
+};
+
+OutRows build_rows(const EventRec *rec, const mkf_tracks &out)
+{
+    return OutRows{rec->view.out_rec, rec->view.out_hits, rec->shape.n_seeds, out};
+}
+
+// Delivers one set of rows and waits for the stream.
+mkf_status deliver_one(mkf_ctx *ctx, const OutRows &o)
+{
+    Delivery d(ctx);
+    d.add(o);
+    return d.finish();
+}
+
+// The rows of a batch's events (outs may be null) and the wait for the stream.
+mkf_status deliver_batch(mkf_ctx *ctx, EventRec *const *recs, int n, const mkf_tracks *outs)
+{
+    Delivery d(ctx);
+    for (int i = 0; outs && i < n; ++i) d.add(build_rows(recs[i], outs[i]));
+    return d.finish();
+}
+
+}  // namespace
 
 static mkf_status check_tracks(const mkf_tracks *out, int n, const char *what)
 {
@@ -1105,6 +1288,8 @@ void mkf_destroy(mkf_ctx *ctx)
     ctx->heap.release(ctx->batch_dev);
     if (ctx->batch_host) (void)hipHostFree(ctx->batch_host);
     if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
+    for (hipEvent_t e : ctx->out_done)
+        if (e) (void)hipEventDestroy(e);
     for (auto &t : ctx->timers)
         for (int i = 0; i < Timer::kRing; ++i) {
             if (t.start[i]) (void)hipEventDestroy(t.start[i]);
@@ -1147,19 +1332,17 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
     std::vector<size_t> off(n + 1, 0);
     size_t values = 0;
     for (int i = 0; i < n; ++i) {
-        mkf_status st = validate_event(ctx, &evs[i], &shapes[i]);
+        const mkf_status st = validate_event(ctx, &evs[i], &shapes[i]);
         if (st != MKF_OK) return n == 1 ? st : fail(st, "event %d: %s", i, mkf_last_error(ctx));
         off[i + 1] = off[i] + ((event_input_bytes(shapes[i]) + 255) & ~size_t(255));
         values += (size_t)shapes[i].n_hits() * 3 + (size_t)(shapes[i].n_seeds + shapes[i].n_tracks) * 27;
     }
-    // every load ends waiting for the stream, so the staging is free
-    if (ctx->load_pin_bytes < off[n]) {
-        if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
-        ctx->load_pin = nullptr;
-        ctx->load_pin_bytes = 0;
-        MKF_HIP(hipHostMalloc(&ctx->load_pin, off[n], hipHostMallocDefault));
-        ctx->load_pin_bytes = off[n];
-    }
+    // room for the results of these events too, so that the first build of a
+    // batch allocates none
+    size_t rows = 0;
+    for (const EventShape &sh : shapes) rows += (size_t)std::max(sh.n_seeds, sh.n_tracks);
+    mkf_status st = ensure_pin(ctx, std::max(off[n], out_pin_bytes(rows, ctx->cfg.n_layers)));
+    if (st != MKF_OK) return st;
     char *pin = static_cast<char *>(ctx->load_pin);
     std::vector<std::unique_ptr<EventRec>> recs(n);
     auto undo = [&](mkf_status st) {
@@ -1169,7 +1352,6 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
         return st;
     };
     hipStream_t s = ctx->stream;
-    mkf_status st;
     // device memory first (the allocator may call back into the caller, so
     // on this thread); then every event is packed and its copy queued as soon
     // as its packing ends, so that the copies overlap the packing of the
@@ -1318,10 +1500,8 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
         MKF_HIP(hipGraphLaunch(rec->plain_graph, ctx->stream));
         timer_end(ctx, 0, ctx->stream, n_launch);
     }
-    if (out && (st = copy_tracks_out(ctx, rec, out, ctx->stream)) != MKF_OK) return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
+    if ((st = deliver_batch(ctx, &rec, 1, out)) != MKF_OK) return st;
     timers_collect(ctx, true);
-    finish_ndof(out);
     return MKF_OK;
 }
 
@@ -1408,13 +1588,8 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
         timers_collect(ctx, false);
         return MKF_OK;
     }
-    if (outs)
-        for (int i = 0; i < n; ++i)
-            if ((st = copy_tracks_out(ctx, recs[i], &outs[i], ctx->stream)) != MKF_OK) return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
+    if ((st = deliver_batch(ctx, recs.data(), n, outs)) != MKF_OK) return st;
     timers_collect(ctx, true);
-    if (outs)
-        for (int i = 0; i < n; ++i) finish_ndof(&outs[i]);
     return MKF_OK;
 }
 
@@ -1468,13 +1643,8 @@ mkf_status mkf_build_batch_noalloc(mkf_ctx *ctx, const int32_t *handles, int32_t
         timers_collect(ctx, false);
         return MKF_OK;
     }
-    if (outs)
-        for (int i = 0; i < n; ++i)
-            if ((st = copy_tracks_out(ctx, recs[i], &outs[i], ctx->stream)) != MKF_OK) return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
+    if ((st = deliver_batch(ctx, recs, n, outs)) != MKF_OK) return st;
     timers_collect(ctx, true);
-    if (outs)
-        for (int i = 0; i < n; ++i) finish_ndof(&outs[i]);
     return MKF_OK;
 }
 
@@ -1485,10 +1655,7 @@ mkf_status mkf_fetch_tracks(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
     if (!rec) return fail(MKF_E_NOTFOUND, "unknown event handle %d", handle);
     mkf_status st = check_tracks(out, rec->shape.n_seeds, "fetch");
     if (st != MKF_OK) return st;
-    if ((st = copy_tracks_out(ctx, rec, out, ctx->stream)) != MKF_OK) return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
-    finish_ndof(out);
-    return MKF_OK;
+    return deliver_one(ctx, build_rows(rec, *out));
 }
 
 mkf_status mkf_fetch_fit(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
@@ -1498,20 +1665,7 @@ mkf_status mkf_fetch_fit(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
     if (!rec) return fail(MKF_E_NOTFOUND, "unknown event handle %d", handle);
     mkf_status st = check_tracks(out, rec->shape.n_seeds, "fetch_fit");
     if (st != MKF_OK) return st;
-    const DevEvent &v = rec->view;
-    const size_t n = (size_t)rec->shape.n_seeds, nl = (size_t)rec->shape.n_layers;
-    hipStream_t s = ctx->stream;
-    if ((st = copy_d2h(out->par, v.rf_par, 48 * n, s)) != MKF_OK || (st = copy_d2h(out->cov, v.rf_cov, 168 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->hits, v.out_hits, 4 * nl * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->n_hits, v.rf_nupd, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->n_holes, v.out_nholes, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->chi2, v.rf_chi2, 8 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->status, v.rf_status, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->ndof, v.rf_nupd, 4 * n, s)) != MKF_OK)
-        return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
-    finish_ndof(out);
-    return MKF_OK;
+    return deliver_one(ctx, OutRows{rec->view.rf_rec, rec->view.out_hits, rec->shape.n_seeds, *out});
 }
 
 mkf_status mkf_fetch_beam(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
@@ -1520,24 +1674,10 @@ mkf_status mkf_fetch_beam(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
     EventRec *rec = find_event(ctx, handle);
     if (!rec) return fail(MKF_E_NOTFOUND, "unknown event handle %d", handle);
     if (!rec->beam) return fail(MKF_E_STATE, "no build of this event kept its beam (MKF_BATCH_BEAM)");
-    const size_t n = (size_t)rec->shape.n_seeds * ctx->cfg.max_cands, nl = (size_t)rec->shape.n_layers;
+    const size_t n = (size_t)rec->shape.n_seeds * ctx->cfg.max_cands;
     mkf_status st = check_tracks(out, (int)n, "fetch_beam");
     if (st != MKF_OK) return st;
-    const DevEvent &v = rec->beam_view;
-    hipStream_t s = ctx->stream;
-    if ((st = copy_d2h(out->par, v.beam_par, 48 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->cov, v.beam_cov, 168 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->hits, v.beam_hits, 4 * nl * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->n_hits, v.beam_nhits, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->n_holes, v.beam_nholes, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->chi2, v.beam_chi2, 8 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->status, v.beam_status, 4 * n, s)) != MKF_OK ||
-        (st = copy_d2h(out->ndof, v.beam_nhits, 4 * n, s)) != MKF_OK)
-        return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
-    if (out->ndof)
-        for (size_t i = 0; i < n; ++i) out->ndof[i] = out->status && out->status[i] < 0 ? 0 : 2 * out->ndof[i] - 5;
-    return MKF_OK;
+    return deliver_one(ctx, OutRows{rec->beam_view.beam_rec, rec->beam_view.beam_hits, (int)n, *out});
 }
 
 mkf_status mkf_index_grid(mkf_ctx *ctx, int32_t handle, int32_t *bins_phi, int32_t *bins_z)
@@ -1602,30 +1742,6 @@ mkf_status mkf_get_stats(mkf_ctx *ctx, int32_t handle, mkf_build_stats *out)
     return MKF_OK;
 }
 
-static mkf_status copy_fit_out(const EventRec *rec, const DevEvent &v, const mkf_tracks *out, hipStream_t s)
-{
-    const size_t n = (size_t)rec->shape.n_tracks, nl = (size_t)rec->shape.n_layers;
-    mkf_status st;
-    if ((st = copy_d2h(out->par, v.fit_par, 48 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->cov, v.fit_cov, 168 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->hits, v.track_hits, 4 * nl * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->n_hits, v.fit_nupd, 4 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->n_holes, v.fit_nupd, 4 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->chi2, v.fit_chi2, 8 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->status, v.fit_status, 4 * n, s)) != MKF_OK) return st;
-    if ((st = copy_d2h(out->ndof, v.fit_nupd, 4 * n, s)) != MKF_OK) return st;
-    return MKF_OK;
-}
-
-static void finish_fit_out(const mkf_tracks *out, int n_layers)
-{
-    if (!out) return;
-    for (int i = 0; i < out->n; ++i) {
-        if (out->n_holes) out->n_holes[i] = n_layers - out->n_holes[i];
-        if (out->ndof) out->ndof[i] = 2 * out->ndof[i] - 5;
-    }
-}
-
 mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tracks *outs)
 {
     if (!ctx) return fail(MKF_E_INVALID, "NULL context");
@@ -1644,13 +1760,11 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     timer_begin(ctx, 2, ctx->stream);
     MKF_HIP(launch_fit(ctx->params, args, ctx->stream));
     timer_end(ctx, 2, ctx->stream, 1);
-    if (outs)
-        for (int i = 0; i < n; ++i)
-            if ((st = copy_fit_out(recs[i], recs[i]->view, &outs[i], ctx->stream)) != MKF_OK) return st;
-    MKF_HIP(hipStreamSynchronize(ctx->stream));
+    Delivery d(ctx);
+    for (int i = 0; outs && i < n; ++i)
+        d.add(OutRows{recs[i]->view.fit_rec, recs[i]->view.track_hits, recs[i]->shape.n_tracks, outs[i]});
+    if ((st = d.finish()) != MKF_OK) return st;
     timers_collect(ctx, true);
-    if (outs)
-        for (int i = 0; i < n; ++i) finish_fit_out(&outs[i], recs[i]->shape.n_layers);
     return MKF_OK;
 }
 
@@ -1683,22 +1797,13 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
         v->track_cov = reinterpret_cast<float *>(take(84 * nt));
         v->track_hits = reinterpret_cast<int *>(take(4 * nl * nt));
         const size_t inputs = o;
-        v->fit_par = reinterpret_cast<double *>(take(48 * nt));
-        v->fit_cov = reinterpret_cast<double *>(take(168 * nt));
-        v->fit_chi2 = reinterpret_cast<double *>(take(8 * nt));
-        v->fit_nupd = reinterpret_cast<int *>(take(4 * nt));
-        v->fit_status = reinterpret_cast<int *>(take(4 * nt));
+        v->fit_rec = reinterpret_cast<float *>(take(4 * (size_t)kRecWords * nt));
         return std::make_pair(inputs, o);
     };
     DevEvent hv{};
     const auto sizes = layout(nullptr, &hv);
-    if (ctx->load_pin_bytes < sizes.first) {
-        if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
-        ctx->load_pin = nullptr;
-        ctx->load_pin_bytes = 0;
-        MKF_HIP(hipHostMalloc(&ctx->load_pin, sizes.first, hipHostMallocDefault));
-        ctx->load_pin_bytes = sizes.first;
-    }
+    // the inputs now, the results later
+    if ((st = ensure_pin(ctx, std::max(sizes.first, out_pin_bytes(nt, (int)nl)))) != MKF_OK) return st;
     layout(static_cast<char *>(ctx->load_pin), &hv);
     std::vector<int32_t> nh(nl);
     for (size_t L = 0; L < nl; ++L) nh[L] = rec->shape.layer_off[L + 1] - rec->shape.layer_off[L];
@@ -1736,11 +1841,12 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     hipError_t e = launch_fit(ctx->params, args, s);
     timer_end(ctx, 2, s, 1);
     if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit launch: %s", hipGetErrorString(e)));
-    if (out && (st = copy_fit_out(&tmp, v, out, s)) != MKF_OK) return cleanup(st);
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit: %s", hipGetErrorString(e)));
+    {
+        Delivery d(ctx);
+        if (out) d.add(OutRows{v.fit_rec, v.track_hits, n_tracks, *out});
+        if ((st = d.finish()) != MKF_OK) return cleanup(st);
+    }
     timers_collect(ctx, true);
-    finish_fit_out(out, ts.n_layers);
     return cleanup(MKF_OK);
 }
 

@@ -117,6 +117,29 @@ struct Timer {
     long long launches = 0;
 };
 
+// Rows of results bound for a caller's arrays: n rows at `rec` / `hits` on
+// the device, `out` the arrays (pointers at the first of these rows).
+struct OutRows {
+    const float *rec = nullptr;
+    const int *hits = nullptr;
+    int n = 0;
+    mkf_tracks out{};
+};
+
+struct HostCopy {   // staged bytes to copy once the device has written them
+    void *dst;
+    const void *src;
+    size_t bytes;
+};
+
+// The way out of results (k_deliver): arrays that the device can write
+// (page-locked memory) are written directly, the others through page-locked
+// staging (the context's) that the host copies from.  The staging is used as
+// a ring of slots, so that the device fills one while the host empties
+// another and large outputs need no staging of their size.
+constexpr int kOutSlots = 4;
+constexpr size_t kOutSlotMin = size_t(512) << 10, kOutSlotMax = size_t(4) << 20;
+
 struct Server;   // serving state (mkf_serve.cpp)
 struct ServerDeleter {
     void operator()(Server *s) const;
@@ -151,8 +174,12 @@ struct mkf_ctx {
     hipEvent_t stage_done = nullptr;    // last copy out of batch_host
     bool stage_pending = false;
     std::vector<char> staged_image;     // what batch_dev holds (empty: unknown)
-    void *load_pin = nullptr;           // pinned staging of the packed inputs of loads and fits
+    // pinned staging of the packed inputs of loads and fits on their way in and
+    // of results on their way out; every call that uses it ends waiting for
+    // the stream, so it is free at the start of the next
+    void *load_pin = nullptr;
     size_t load_pin_bytes = 0;
+    hipEvent_t out_done[mkf::kOutSlots] = {};   // a slot of the result staging filled by the device
     std::vector<std::unique_ptr<mkf::BatchGraph>> graphs;
     mkf::Timer timers[3];
     std::unique_ptr<mkf::Server, mkf::ServerDeleter> server;
@@ -185,7 +212,17 @@ mkf_status run_pipeline(mkf_ctx *ctx, const BatchArgs &args, const std::vector<E
 // the same with explicit parameters and launch shapes (serving keeps its own)
 mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args,
                              uint32_t flags, bool timed, hipStream_t s);
-mkf_status copy_tracks_out(mkf_ctx *ctx, const EventRec *rec, const mkf_tracks *out, hipStream_t s);
+// The fields of a result row (par, cov, chi2 in FP64, then hits, n_hits,
+// n_holes, ndof, status): bytes per row, array in mkf_tracks, array of a job.
+constexpr int kOutFields = 8;
+constexpr int kOutDoubles = 3;
+size_t field_bytes(int f, int n_layers);
+void *field_of(const mkf_tracks &t, int f);
+void set_field(DeliverJob &j, int f, void *p);
+// the device's address of `bytes` of host memory at p when all of it is
+// page-locked for this device (or device memory of it) and p a multiple of
+// `align`, else null
+void *device_writable(void *p, size_t bytes, size_t align, int device);
 void shutdown_server(mkf_ctx *ctx);
 
 }  // namespace mkf

@@ -71,39 +71,16 @@ struct Ticket {
     mkf_tracks out{};
     void *in_pin = nullptr;
     size_t in_cls = 0;
-    void *out_pin = nullptr;
+    void *out_pin = nullptr;      // staging of the output arrays that are not page-locked
     size_t out_cls = 0;
+    void *dst[kOutFields] = {};   // where the device writes each field: the caller's array or the staging
+    std::vector<HostCopy> copies; // from the staging to the caller's arrays
     size_t reserved = 0;          // budget bytes held from submit to completion
     Clock::time_point t_submit, t_done;
     int state = 0;                // 0 admitted, 1 running, 2 done
     mkf_status status = MKF_OK;
     std::unique_ptr<EventRec> rec;
 };
-
-struct OutLayout {
-    size_t par, cov, hits, nhits, nholes, chi2, status, total;
-};
-
-OutLayout out_layout(const EventShape &s)
-{
-    OutLayout l{};
-    size_t off = 0;
-    const size_t n = (size_t)s.n_seeds;
-    auto take = [&](size_t b) {
-        const size_t o = off;
-        off = round256(off + b);
-        return o;
-    };
-    l.par = take(48 * n);
-    l.cov = take(168 * n);
-    l.hits = take(4 * (size_t)s.n_layers * n);
-    l.nhits = take(4 * n);
-    l.nholes = take(4 * n);
-    l.chi2 = take(8 * n);
-    l.status = take(4 * n);
-    l.total = off;
-    return l;
-}
 
 struct Running {
     std::vector<Ticket *> tickets;
@@ -139,11 +116,16 @@ struct Server {
     PinnedPool pinned;
     std::thread thr;
 
-    // device bytes of one event: its data and its hit index, as the slab
-    // rounds them
+    // what one event takes of the budget: its data and its hit index, as the
+    // slab rounds them, the results of the build and of a final fit counted
+    // in the caller's types (FP64: 27 words more a row than their FP32 rows on
+    // the device for the build's, 26 for the fit's), so that a budget admits
+    // the same events whatever form the device keeps them in
     size_t footprint(const EventShape &s) const
     {
-        return round256(event_data_bytes(s)) + round256(event_index_bytes(s, event_bins(s, tuning.bins_phi, tuning.bins_z)));
+        const size_t wide = round256((27 + 26) * sizeof(int) * (size_t)s.n_seeds);
+        return round256(event_data_bytes(s)) + wide +
+               round256(event_index_bytes(s, event_bins(s, tuning.bins_phi, tuning.bins_z)));
     }
 
     void release_ticket_resources(Ticket *t)
@@ -174,20 +156,7 @@ struct Server {
     void finish_batch(Running &b)
     {
         for (Ticket *t : b.tickets) {
-            const OutLayout ol = out_layout(t->shape);
-            const char *o = static_cast<const char *>(t->out_pin);
-            const size_t n = (size_t)t->shape.n_seeds;
-            if (t->out.par) std::memcpy(t->out.par, o + ol.par, 48 * n);
-            if (t->out.cov) std::memcpy(t->out.cov, o + ol.cov, 168 * n);
-            if (t->out.hits) std::memcpy(t->out.hits, o + ol.hits, 4 * (size_t)t->shape.n_layers * n);
-            if (t->out.n_hits) std::memcpy(t->out.n_hits, o + ol.nhits, 4 * n);
-            if (t->out.n_holes) std::memcpy(t->out.n_holes, o + ol.nholes, 4 * n);
-            if (t->out.chi2) std::memcpy(t->out.chi2, o + ol.chi2, 8 * n);
-            if (t->out.status) std::memcpy(t->out.status, o + ol.status, 4 * n);
-            if (t->out.ndof) {
-                const int *nh = reinterpret_cast<const int *>(o + ol.nhits);
-                for (size_t i = 0; i < n; ++i) t->out.ndof[i] = 2 * nh[i] - 5;
-            }
+            for (const HostCopy &c : t->copies) std::memcpy(c.dst, c.src, c.bytes);
             release_ticket_resources(t);
         }
         (void)hipEventDestroy(b.done);
@@ -218,19 +187,24 @@ struct Server {
                                     seeds_per_item(tuning.lanes_per_seed), &args, s);
         if (st != MKF_OK) return st;
         if ((st = run_pipeline_with(ctx, params, tuning, args, MKF_BATCH_REINDEX, false, s)) != MKF_OK) return st;
-        for (Ticket *t : batch) {
-            const OutLayout ol = out_layout(t->shape);
-            char *o = static_cast<char *>(t->out_pin);
+        DeliverArgs da;
+        da.n_jobs = da.n_tiles = 0;
+        da.n_layers = ctx->cfg.n_layers;
+        for (size_t i = 0; i < batch.size(); ++i) {
+            const Ticket *t = batch[i];
             const DevEvent &v = t->rec->view;
-            const size_t n = (size_t)t->shape.n_seeds;
-            if (!n) continue;
-            MKF_HIP(hipMemcpyAsync(o + ol.par, v.out_par, 48 * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.cov, v.out_cov, 168 * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.hits, v.out_hits, 4 * (size_t)t->shape.n_layers * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.nhits, v.out_nhits, 4 * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.nholes, v.out_nholes, 4 * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.chi2, v.out_chi2, 8 * n, hipMemcpyDeviceToHost, s));
-            MKF_HIP(hipMemcpyAsync(o + ol.status, v.out_status, 4 * n, hipMemcpyDeviceToHost, s));
+            DeliverJob &j = da.job[da.n_jobs++];
+            j = DeliverJob{};
+            j.rec = v.out_rec;
+            j.hits = v.out_hits;
+            j.n = t->shape.n_seeds;
+            j.first_tile = da.n_tiles;
+            da.n_tiles += (j.n + kDeliverTile - 1) / kDeliverTile;
+            for (int f = 0; f < kOutFields; ++f) set_field(j, f, t->dst[f]);
+            if (da.n_jobs == kDeliverJobs || i + 1 == batch.size()) {
+                MKF_HIP(launch_deliver(da, s));
+                da.n_jobs = da.n_tiles = 0;
+            }
         }
         MKF_HIP(hipEventCreateWithFlags(&run->done, hipEventDisableTiming));
         MKF_HIP(hipEventRecord(run->done, s));
@@ -432,14 +406,29 @@ mkf_status mkf_serve_submit(mkf_ctx *ctx, const mkf_event *ev, mkf_tracks *out, 
         sv->reserved -= need;
         sv->cv.notify_all();
     };
-    const OutLayout ol = out_layout(shape);
+    size_t staged = 0, stage_off[kOutFields];
+    for (int f = 0; f < kOutFields; ++f) {
+        void *p = field_of(*out, f);
+        const size_t bytes = field_bytes(f, shape.n_layers) * (size_t)shape.n_seeds;
+        if (!p || !bytes) continue;
+        t->dst[f] = device_writable(p, bytes, f < kOutDoubles ? 8 : 4, ctx->device);
+        stage_off[f] = staged;
+        if (!t->dst[f]) staged += round256(bytes);
+    }
     t->in_pin = sv->pinned.get(event_input_bytes(shape), &t->in_cls);
-    t->out_pin = sv->pinned.get(ol.total, &t->out_cls);
-    if (!t->in_pin || !t->out_pin) {
+    if (staged) t->out_pin = sv->pinned.get(staged, &t->out_cls);
+    if (!t->in_pin || (staged && !t->out_pin)) {
         sv->pinned.put(t->in_pin, t->in_cls);
         sv->pinned.put(t->out_pin, t->out_cls);
         unreserve();
         return fail(MKF_E_NOMEM, "pinned staging");
+    }
+    for (int f = 0; f < kOutFields; ++f) {
+        void *p = field_of(*out, f);
+        const size_t bytes = field_bytes(f, shape.n_layers) * (size_t)shape.n_seeds;
+        if (!p || !bytes || t->dst[f]) continue;
+        t->dst[f] = static_cast<char *>(t->out_pin) + stage_off[f];
+        t->copies.push_back(HostCopy{p, t->dst[f], bytes});
     }
     // the values are checked while they are narrowed to FP32 into the staging
     mkf_event seeds_only = *ev;
