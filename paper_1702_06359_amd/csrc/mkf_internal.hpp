@@ -64,8 +64,11 @@ struct DevEvent {
                                          // disk; (x, y, z, 0) for thick layers and the 3x3 measurement
     float4 *binned;                      // [n_hits] grouped by layer then bin: (c, s, z or r, id bits)
     int *bin_of;                         // [n_hits] bin of each caller-order hit
-    int *bin_rank;                       // [n_hits] position of the hit inside its bin
-    int *bin_count;                      // [n_layers][n_bins] counts (zero between index builds)
+    // the bucketed index build's working arrays (k_index_hist, _part, _place)
+    float4 *part;                        // [n_hits] hits grouped by layer then bucket, as in `binned`; null: none
+    int *part_bin;                       // [n_hits] and their bins
+    int *hist;                           // [n_layers][idx_chunks][kBuckets] hits per chunk and bucket
+    int *bucket_off;                     // [n_layers][kBuckets + 1] first hit of each bucket in its layer
     int *bin_off;                        // [n_layers][bin_off_stride(n_bins)]: n_bins + 1 absolute indices into
                                          // `binned` per layer
     const float *seed_par;               // [n_seeds][6]
@@ -94,7 +97,28 @@ struct DevEvent {
     int *st_hist;                        // [n_layers][slots] parent rank << 24 | hit (0xFFFFFF: hole)
     int st_slots;
     int grid_k;                          // the event's bin grid: (bins_phi >> grid_k) x (bins_z >> grid_k)
+    int bucket_shift;                    // log2 of the bins of a bucket
+    int idx_chunk, idx_chunks;           // hits of a chunk of a layer; chunks of the fullest layer
 };
+
+// The bucketed index build sorts a layer's hits by bucket (a run of
+// 2^bucket_shift bins, at most kBuckets of them) and then each bucket by bin.
+// A chunk is the hits one block counts: 2,048, more for layers over kBuckets
+// chunks' worth, so that a block sums at most 64 x 64 counts.
+constexpr int kBuckets = 64;
+constexpr int kBlockThreads = 256;
+inline int bucket_shift_of(int n_bins)
+{
+    int s = 3;   // a bucket's first bin offset is 16-byte aligned, its counts come in eights
+    while ((kBuckets << s) < n_bins) ++s;
+    return s;
+}
+inline int idx_chunk_of(int max_layer_hits)
+{
+    const int most = (max_layer_hits + 63) / 64;
+    const int c = most > 2048 ? most : 2048;
+    return (c + kBlockThreads - 1) / kBlockThreads * kBlockThreads;
+}
 
 // A result row on the device: the state (6 words), the packed covariance
 // (21), then the words named here; the counts and the status are integer
@@ -131,6 +155,28 @@ struct DeliverArgs {
     int n_layers;
 };
 
+// Largest layer and bin grid of some events.
+struct IndexExtent {
+    int layer_hits = 0;
+    int bins = 0;
+    int events = 0;
+    void add(int hits, int nb)
+    {
+        layer_hits = hits > layer_hits ? hits : layer_hits;
+        bins = nb > bins ? nb : bins;
+        ++events;
+    }
+};
+
+// LDS counters of a layer indexed by one block: two 16-bit ones a word for
+// layers of at most 65,535 hits.
+inline size_t layer_block_lds(int layer_hits, int bins)
+{
+    return sizeof(int) * (size_t)(layer_hits <= 0xFFFF ? (bins + 1) / 2 : bins);
+}
+constexpr size_t kLayerBlockLds = size_t(128) << 10;   // of a block's 160 KB
+inline bool layer_block_fits(int layer_hits, int bins) { return layer_block_lds(layer_hits, bins) <= kLayerBlockLds; }
+
 // A batch: events plus the flattened work decomposition over them.
 struct BatchArgs {
     const DevEvent *events;
@@ -145,8 +191,11 @@ struct BatchArgs {
     int total_tracks;
     int total_seeds;
     int seeds_per_item;
-    int max_layer_hits;          // largest layer of any event (index launch shape)
-    int max_bins;                // largest bin grid of any event (index launch shape)
+    // index launch shapes
+    IndexExtent all;             // of every event
+    IndexExtent layer_only;      // of the events without arrays for the bucketed build
+    int max_chunks;              // most chunks and bins per bucket of the other events
+    int max_bucket_shift;
 };
 
 // Ints per layer in the bin-offset array: its n_bins + 1 offsets, padded to

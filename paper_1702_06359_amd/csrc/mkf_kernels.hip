@@ -43,6 +43,24 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v,
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// Exclusive prefix sum over the wavefront with DPP moves (no LDS round
+// trips): within each row of 16 lanes by shifts of 1, 2, 3, 4 and 8 lanes,
+// then across rows by broadcasting lane 15 into rows 1 and 3 and lane 31
+// into rows 2 and 3.  Disabled lanes of a step add 0.
+__device__ __forceinline__ int wave_exclusive_sum(int x, int lane)
+{
+    (void)lane;
+    int v = x;
+    v += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, x, 0x113, 0xf, 0xf, true);   // row_shr:3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xe, true);   // row_shr:4, banks 1-3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xc, true);   // row_shr:8, banks 2-3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast:31 into rows 2, 3
+    return v - x;
+}
+
 __global__ void k_fill_i32(int *__restrict__ p, int v, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -130,20 +148,6 @@ __device__ __forceinline__ int bin_hit(const Params &P, const LayerParam &lp, co
     ip = min(max(ip, 0), g.bp - 1);
     iz = min(max(iz, 0), g.bz - 1);
     return iz * g.bp + ip;
-}
-
-// Binning of every hit of a batch, no atomics: grid (chunks, event x
-// layer).  Precedes k_index_range.
-__global__ void __launch_bounds__(256) k_index_bin(const Params P, const BatchArgs B)
-{
-    const int e = blockIdx.y / P.n_layers;
-    const int L = blockIdx.y - e * P.n_layers;
-    CEvent &E = event_desc(B.events, e);
-    const int h0 = E.layer_off[L], h1 = E.layer_off[L + 1];
-    const LayerParam lp = P.layer[L];
-    const EvGrid g = ev_grid(P, E);
-    for (int h = h0 + blockIdx.x * blockDim.x + threadIdx.x; h < h1; h += gridDim.x * blockDim.x)
-        store_global(E.bin_of + h, bin_hit(P, lp, g, load_global(E.hits + h)));
 }
 
 // Bin counters in LDS: one 32-bit counter per bin, or two 16-bit counters per
@@ -255,110 +259,9 @@ __device__ __forceinline__ void lds_scan_counts(unsigned *s_cnt, int nr, int car
     }
 }
 
-// Hit index of a layer, its bins split into `nsplit` ranges of `chunk` bins
-// (a multiple of 64), after k_index_bin: one 1024-thread block per (event,
-// layer, range) reads the bin of every hit of the layer, counts those in its
-// range with LDS atomics and those below it, scans its range's counts in LDS
-// (the absolute offsets written out as they are formed), then reads the bins
-// again and places the hits of its range at their bin's running offset (a
-// second LDS atomic).  No device-wide atomic, no count array to clear, no
-// rank stored, and no block waits for another; the split fills the machine
-// when a batch has few (event, layer) pairs.  The order inside a bin is that
-// of the atomics, which does not matter: every hit of a window is tested and
-// ties are broken by hit index.  kShort packs two 16-bit counters per word
-// (layers of at most 65,535 hits).
-template <bool kShort>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) k_index_range(const Params P,
-                                                                                              const BatchArgs B,
-                                                                                              int nsplit, int chunk)
-{
-    extern __shared__ unsigned s_cnt[];
-    __shared__ int s_wave[16];
-    const int part = blockIdx.x % nsplit;
-    const int el = blockIdx.x / nsplit;
-    const int e = el / P.n_layers;
-    const int L = el - e * P.n_layers;
-    CEvent &E = event_desc(B.events, e);
-    const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
-    const EvGrid g = ev_grid(P, E);
-    const int nb = g.bp * g.bz;
-    int *off = E.bin_off + L * bin_off_stride(nb);
-    const int *bin_of = E.bin_of + h0;
-    const float4 *hits = E.hits + h0;
-    float4 *binned = E.binned + h0;
-    if (part == nsplit - 1 && threadIdx.x == 0) off[nb] = h0 + n;
-    const int lo = part * chunk;
-    if (lo >= nb) return;                     // an empty range (whole block)
-    const int nr = min(chunk, nb - lo);       // bins of this range
-    const int nw = kShort ? (nr + 1) / 2 : nr;
-    for (int i = threadIdx.x; i < nw; i += blockDim.x) s_cnt[i] = 0u;
-    __syncthreads();
-    constexpr int kU = 8;
-    const int stride = blockDim.x, step = kU * stride;
-    const int n_full = n - n % step;
-    int below = 0;   // hits of this thread in bins before the range
-    for (int i = threadIdx.x; i < n_full; i += step) {
-        int b[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) b[u] = load_global(bin_of + i + u * stride) - lo;
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            below += b[u] < 0 ? 1 : 0;
-            if ((unsigned)b[u] < (unsigned)nr) lds_bump<kShort>(s_cnt, b[u]);
-        }
-    }
-    for (int i = n_full + threadIdx.x; i < n; i += stride) {
-        const int b = load_global(bin_of + i) - lo;
-        below += b < 0 ? 1 : 0;
-        if ((unsigned)b < (unsigned)nr) lds_bump<kShort>(s_cnt, b);
-    }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-    // block sum of `below`: the offset of the range's first bin in the layer
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) below += __shfl_xor(below, o);
-    if (lane == 0) s_wave[wave] = below;
-    __syncthreads();
-    int carry = 0;
-    for (int w = 0; w < n_waves; ++w) carry += s_wave[w];
-    __syncthreads();
-    // exclusive scan of the counts into offsets relative to the layer, written
-    // out absolute; ends on a barrier
-    lds_scan_counts<kShort, 16>(s_cnt, nr, carry, s_wave, off + lo, h0);
-    // placement: kP hits per thread and step
-    constexpr int kP = 4;
-    const int pstep = kP * stride;
-    const int p_full = n - n % pstep;
-    for (int i = threadIdx.x; i < p_full; i += pstep) {
-        int b[kP];
-#pragma unroll
-        for (int u = 0; u < kP; ++u) b[u] = load_global(bin_of + i + u * stride) - lo;
-        // the hit loads issued together, outside any branch: lanes whose hit
-        // lies in another range all read the layer's first hit (one line)
-        float4 v[kP];
-#pragma unroll
-        for (int u = 0; u < kP; ++u) v[u] = load_global(hits + ((unsigned)b[u] < (unsigned)nr ? i + u * stride : 0));
-        // all the atomics, then all the stores: a store between them would
-        // make each later branch wait for it
-        int pos[kP];
-#pragma unroll
-        for (int u = 0; u < kP; ++u) pos[u] = (unsigned)b[u] < (unsigned)nr ? lds_bump<kShort>(s_cnt, b[u]) : -1;
-#pragma unroll
-        for (int u = 0; u < kP; ++u)
-            if (pos[u] >= 0)
-                store_global(binned + pos[u], make_float4(v[u].x, v[u].y, v[u].z, __int_as_float(i + u * stride)));
-    }
-    for (int i = p_full + threadIdx.x; i < n; i += stride) {
-        const int b = load_global(bin_of + i) - lo;
-        if ((unsigned)b < (unsigned)nr) {
-            const float4 v = load_global(hits + i);
-            const int pos = lds_bump<kShort>(s_cnt, b);
-            store_global(binned + pos, make_float4(v.x, v.y, v.z, __int_as_float(i)));
-        }
-    }
-}
-
 // Hit index of one layer in one 1024-thread block per (event, layer), for
-// batches with enough (event, layer) pairs to fill the machine: every hit
+// batches of many (event, layer) pairs or of small layers (`only`: events
+// without arrays for the bucketed build): every hit
 // binned (bin_of kept) and counted with LDS atomics, the counts scanned in LDS
 // (the offsets written out as they are formed), then every hit placed at its
 // bin's running offset (a second LDS atomic), so that no rank is stored.  The
@@ -369,13 +272,15 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
 // thread reads back only the bins it wrote itself.
 template <bool kShort>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) k_index_layer(const Params P,
-                                                                                                   const BatchArgs B)
+                                                                                                   const BatchArgs B,
+                                                                                                   int only)
 {
     extern __shared__ unsigned s_cnt[];
     __shared__ int s_wave[16];
     const int e = blockIdx.x / P.n_layers;
     const int L = blockIdx.x - e * P.n_layers;
     CEvent &E = event_desc(B.events, e);
+    if (only && E.part) return;               // the whole block: the bucketed build has this event
     const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
     const LayerParam lp = P.layer[L];
     const EvGrid g = ev_grid(P, E);
@@ -443,117 +348,163 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     }
 }
 
-// Pass 1: bin each caller-order hit and take its position in the bin.  Grid
-// (chunks, event x layer).
-__global__ void __launch_bounds__(256) k_index_prep(const Params P, const BatchArgs B)
+// Hit index of layers that each get many blocks, in three launches.  First
+// (k_index_hist) every chunk of a layer's hits is binned and its hits per
+// bucket of bins counted in LDS; then (k_index_part) each chunk takes its place
+// in every bucket from the counts of the chunks before it and writes its hits
+// there; then (k_index_place) a block per bucket counts its hits per bin, scans
+// the counts into the bin offsets and places the hits.  Every hit is read by
+// one block per launch (splitting the bins over blocks that each read the
+// whole layer instead took 51 us for one 50,000-track event, its time the
+// 2 x 64 hits each thread went through whatever the split), no counter leaves
+// LDS, and the last pass writes into one run of lines per block, which so
+// leave its L2 whole.
+__global__ void __launch_bounds__(kBlockThreads) k_index_hist(const Params P, const BatchArgs B)
 {
+    __shared__ int s_n[kBuckets];
     const int e = blockIdx.y / P.n_layers;
     const int L = blockIdx.y - e * P.n_layers;
     CEvent &E = event_desc(B.events, e);
-    const int h0 = E.layer_off[L], h1 = E.layer_off[L + 1];
+    const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
+    const int i0 = blockIdx.x * E.idx_chunk, i1 = min(i0 + E.idx_chunk, n);
+    if (!E.part || i0 >= n) return;           // the whole block
     const LayerParam lp = P.layer[L];
     const EvGrid g = ev_grid(P, E);
-    int *cnt = E.bin_count + L * g.bp * g.bz;
-    for (int h = h0 + blockIdx.x * blockDim.x + threadIdx.x; h < h1; h += gridDim.x * blockDim.x) {
-        const int bin = bin_hit(P, lp, g, load_global(E.hits + h));
-        E.bin_of[h] = bin;
-        E.bin_rank[h] = atomicAdd(&cnt[bin], 1);
+    if (threadIdx.x < kBuckets) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    const float4 *hits = E.hits + h0;
+    int *bin_of = E.bin_of + h0;
+    constexpr int kU = 8;
+    for (int base = i0; base < i1; base += kU * kBlockThreads) {
+        float4 v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = load_global(hits + min(base + u * kBlockThreads + (int)threadIdx.x, i1 - 1));
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int i = base + u * kBlockThreads + threadIdx.x;
+            const int b = bin_hit(P, lp, g, v[u]);
+            if (i < i1) {
+                store_global(bin_of + i, b);
+                atomicAdd(&s_n[b >> E.bucket_shift], 1);
+            }
+        }
     }
+    __syncthreads();
+    if (threadIdx.x < kBuckets)
+        store_global(E.hist + (L * E.idx_chunks + (int)blockIdx.x) * kBuckets + threadIdx.x, s_n[threadIdx.x]);
 }
 
-// Pass 2: one block per (event, layer): exclusive scan of the bin counts into
-// absolute offsets.  Each thread owns 32 consecutive bins, so a layer of up to
-// 32768 bins is one step whose loads are all in flight together; the counts are
-// cleared on the way so the next index build starts from zero.
-__global__ void __launch_bounds__(1024) k_index_scan(const Params P, const BatchArgs B)
+__global__ void __launch_bounds__(kBlockThreads) k_index_part(const Params P, const BatchArgs B)
 {
-    constexpr int kPer = 32;   // consecutive bins per thread
-    __shared__ int s_wave[16];
-    const int e = blockIdx.x / P.n_layers;
-    const int L = blockIdx.x - e * P.n_layers;
-    CEvent &E = event_desc(B.events, e);
-    const EvGrid g = ev_grid(P, E);
-    const int nb = g.bp * g.bz;
-    int *cnt = E.bin_count + L * nb;
-    int *off = E.bin_off + L * bin_off_stride(nb);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int n_waves = blockDim.x >> 6;
-    const bool vec = (nb & 3) == 0;   // then every thread's first bin is 16-byte aligned
-    int carry = E.layer_off[L];
-    for (int base = 0; base < nb; base += blockDim.x * kPer) {
-        const int b0 = base + threadIdx.x * kPer;
-        int v[kPer];
-        if (vec && b0 + kPer <= nb) {
-#pragma unroll
-            for (int j = 0; j < kPer; j += 4) {
-                const int4 q = *reinterpret_cast<const int4 *>(cnt + b0 + j);
-                v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) v[j] = b0 + j < nb ? cnt[b0 + j] : 0;
-        }
-        int sum = 0;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) sum += v[j];
-        int x = sum;   // inclusive scan of the per-thread sums inside the wavefront
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int t = __shfl_up(x, o);
-            if (lane >= o) x += t;
-        }
-        if (lane == kWave - 1) s_wave[wave] = x;
-        __syncthreads();
-        if (wave == 0) {
-            int w = lane < n_waves ? s_wave[lane] : 0;
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                const int t = __shfl_up(w, o);
-                if (lane >= o) w += t;
-            }
-            if (lane < n_waves) s_wave[lane] = w;
-        }
-        __syncthreads();
-        int run = carry + (wave > 0 ? s_wave[wave - 1] : 0) + x - sum;
-        if (vec && b0 + kPer <= nb) {
-#pragma unroll
-            for (int j = 0; j < kPer; j += 4) *reinterpret_cast<int4 *>(cnt + b0 + j) = make_int4(0, 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                off[b0 + j] = run;
-                run += v[j];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                if (b0 + j < nb) {
-                    off[b0 + j] = run;
-                    cnt[b0 + j] = 0;
-                }
-                run += v[j];
-            }
-        }
-        carry += s_wave[n_waves - 1];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) off[nb] = E.layer_off[L + 1];
-}
-
-// Pass 3: scatter each hit into its bin (order inside a bin is irrelevant:
-// every hit of a window is tested and ties are broken by hit index).
-__global__ void __launch_bounds__(256) k_index_scatter(const Params P, const BatchArgs B)
-{
+    constexpr int kParts = kBlockThreads / kBuckets;   // threads that share the sums of a bucket
+    __shared__ int s_before[kParts][kBuckets], s_all[kParts][kBuckets], s_next[kBuckets];
     const int e = blockIdx.y / P.n_layers;
     const int L = blockIdx.y - e * P.n_layers;
     CEvent &E = event_desc(B.events, e);
-    const int h0 = E.layer_off[L], h1 = E.layer_off[L + 1];
+    const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
+    const int i0 = blockIdx.x * E.idx_chunk, i1 = min(i0 + E.idx_chunk, n);
+    if (!E.part || i0 >= n) return;           // the whole block
+    const int chunks = (n + E.idx_chunk - 1) / E.idx_chunk;
+    const int b = threadIdx.x % kBuckets, part = threadIdx.x / kBuckets;
+    const int *hist = E.hist + L * E.idx_chunks * kBuckets;
+    int before = 0, all = 0;
+    for (int c = part; c < chunks; c += kParts) {
+        const int v = load_global(hist + c * kBuckets + b);
+        all += v;
+        before += c < (int)blockIdx.x ? v : 0;
+    }
+    s_before[part][b] = before;
+    s_all[part][b] = all;
+    __syncthreads();
+    if (threadIdx.x < kBuckets) {   // one wavefront: kBuckets lanes
+#pragma unroll
+        for (int p = 1; p < kParts; ++p) {
+            before += s_before[p][b];
+            all += s_all[p][b];
+        }
+        const int start = wave_exclusive_sum(all, b);
+        s_next[b] = start + before;
+        if (blockIdx.x == 0) {
+            store_global(E.bucket_off + L * (kBuckets + 1) + b, start);
+            if (b == 0) store_global(E.bucket_off + L * (kBuckets + 1) + kBuckets, n);
+        }
+    }
+    __syncthreads();
+    const int *bin_of = E.bin_of + h0;
+    const float4 *hits = E.hits + h0;
+    float4 *part_hits = E.part + h0;
+    int *part_bins = E.part_bin + h0;
+    constexpr int kU = 8;
+    for (int base = i0; base < i1; base += kU * kBlockThreads) {
+        int bin[kU], pos[kU];
+        float4 v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int i = min(base + u * kBlockThreads + (int)threadIdx.x, i1 - 1);
+            bin[u] = load_global(bin_of + i);
+            v[u] = load_global(hits + i);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            pos[u] = base + u * kBlockThreads + (int)threadIdx.x < i1 ? atomicAdd(&s_next[bin[u] >> E.bucket_shift], 1)
+                                                                    : -1;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (pos[u] < 0) continue;
+            const int i = base + u * kBlockThreads + (int)threadIdx.x;
+            store_global(part_hits + pos[u], make_float4(v[u].x, v[u].y, v[u].z, __int_as_float(i)));
+            store_global(part_bins + pos[u], bin[u]);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kBlockThreads) k_index_place(const Params P, const BatchArgs B)
+{
+    extern __shared__ unsigned s_cnt[];
+    __shared__ int s_wave[16];
+    const int e = blockIdx.y / P.n_layers;
+    const int L = blockIdx.y - e * P.n_layers;
+    CEvent &E = event_desc(B.events, e);
     const EvGrid g = ev_grid(P, E);
     const int nb = g.bp * g.bz;
-    const int *off = E.bin_off + L * bin_off_stride(nb);
-    for (int h = h0 + blockIdx.x * blockDim.x + threadIdx.x; h < h1; h += gridDim.x * blockDim.x) {
-        const int pos = load_global(off + load_global(E.bin_of + h)) + load_global(E.bin_rank + h);
-        const float4 v = load_global(E.hits + h);
-        store_global(E.binned + pos, make_float4(v.x, v.y, v.z, __int_as_float(h - h0)));
+    const int lo = (int)blockIdx.x << E.bucket_shift;
+    if (!E.part || lo >= nb) return;          // the whole block
+    const int nr = min(1 << E.bucket_shift, nb - lo);
+    const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
+    const int *edge = E.bucket_off + L * (kBuckets + 1) + blockIdx.x;
+    const int s0 = n > 0 ? load_global(edge) : 0, s1 = n > 0 ? load_global(edge + 1) : 0;
+    int *off = E.bin_off + L * bin_off_stride(nb);
+    const float4 *part_hits = E.part + h0;
+    const int *part_bins = E.part_bin + h0;
+    float4 *binned = E.binned + h0;
+    if (lo + nr == nb && threadIdx.x == 0) store_global(off + nb, h0 + n);
+    // the bucket's first kP hits per thread stay in registers, their loads in
+    // flight through the count and the scan; a fuller bucket reads the rest
+    // twice
+    constexpr int kP = 4;
+    int bin[kP];
+    float4 v[kP];
+    const int first = s0 + (int)threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kP; ++u) {
+        const int i = first + u * kBlockThreads;
+        bin[u] = i < s1 ? load_global(part_bins + i) - lo : -1;
+        v[u] = i < s1 ? load_global(part_hits + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int i = threadIdx.x; i < nr; i += kBlockThreads) s_cnt[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kP; ++u)
+        if (bin[u] >= 0) atomicAdd(&s_cnt[bin[u]], 1u);
+    for (int i = first + kP * kBlockThreads; i < s1; i += kBlockThreads) atomicAdd(&s_cnt[load_global(part_bins + i) - lo], 1u);
+    __syncthreads();
+    lds_scan_counts<false, 8>(s_cnt, nr, s0, s_wave, off + lo, h0);   // ends on a barrier
+#pragma unroll
+    for (int u = 0; u < kP; ++u)
+        if (bin[u] >= 0) store_global(binned + atomicAdd(&s_cnt[bin[u]], 1u), v[u]);
+    for (int i = first + kP * kBlockThreads; i < s1; i += kBlockThreads) {
+        const float4 h = load_global(part_hits + i);
+        store_global(binned + atomicAdd(&s_cnt[load_global(part_bins + i) - lo], 1u), h);
     }
 }
 
@@ -672,24 +623,6 @@ __device__ __forceinline__ void wave_priority()
 __device__ __forceinline__ int lanes_below(unsigned long long m)
 {
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
-
-// Exclusive prefix sum over the wavefront with DPP moves (no LDS round
-// trips): within each row of 16 lanes by shifts of 1, 2, 3, 4 and 8 lanes,
-// then across rows by broadcasting lane 15 into rows 1 and 3 and lane 31
-// into rows 2 and 3.  Disabled lanes of a step add 0.
-__device__ __forceinline__ int wave_exclusive_sum(int x, int lane)
-{
-    (void)lane;
-    int v = x;
-    v += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, x, 0x113, 0xf, 0xf, true);   // row_shr:3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xe, true);   // row_shr:4, banks 1-3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xc, true);   // row_shr:8, banks 2-3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast:15 into rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast:31 into rows 2, 3
-    return v - x;
 }
 
 // Inclusive prefix maximum over the wavefront of non-negative values, with
@@ -2003,94 +1936,41 @@ hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s)
     return hipGetLastError();
 }
 
-// LDS one block may use on the current device (queried once per device;
-// lowered to the 64 KB default if a larger launch is refused).
-static std::atomic<int> g_lds_limit[64];
-
-static std::atomic<int> g_cu_count[64];
-
-static int compute_units()
+static hipError_t launch_index_layer(const Params &p, const BatchArgs &b, const IndexExtent &x, int only, hipStream_t s)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    int v = g_cu_count[dev & 63].load();
-    if (v <= 0) {
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-        g_cu_count[dev & 63].store(v);
-    }
-    return v;
-}
-
-static size_t lds_per_block()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 65536 - 1024;
-    int v = g_lds_limit[dev & 63].load();
-    if (v <= 0) {
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= 0)
-            v = 65536;
-        g_lds_limit[dev & 63].store(v);
-    }
-    return (size_t)v - 1024;   // room for the kernel's static LDS
-}
-
-static void lds_refused()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) g_lds_limit[dev & 63].store(65536);
+    const unsigned blocks = (unsigned)(b.n_events * p.n_layers);
+    const size_t lds = layer_block_lds(x.layer_hits, x.bins);
+    if (x.layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, lds, s>>>(p, b, only);
+    else k_index_layer<false><<<blocks, 1024, lds, s>>>(p, b, only);
+    return hipGetLastError();
 }
 
 hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s)
 {
     if (b.total_hits <= 0) return hipSuccess;
-    const size_t nb = (size_t)b.max_bins;   // the batch's largest event grid
-    const size_t lds = lds_per_block();
-    const unsigned blocks = (unsigned)(b.n_events * p.n_layers);
-    const int n_cu = compute_units();
-    // chunks per (event, layer) of the per-hit kernels: about one hit per
-    // thread for the largest layer, striding beyond that
-    const dim3 grid(std::max(1u, std::min(4096u, blocks_for(b.max_layer_hits, 256))), blocks);
-    // One block per (event, layer), binning included, from a quarter as many
-    // pairs as compute units: measured on ten 20,000-track events, splitting
-    // their 100 layers' bins over more blocks only adds re-reads of the bins.
-    if ((int)blocks * 4 >= n_cu) {
-        const size_t words = b.max_layer_hits <= 0xFFFF ? (nb + 1) / 2 : nb;
-        if (words * 4 <= lds) {
-            if (b.max_layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, words * 4, s>>>(p, b);
-            else k_index_layer<false><<<blocks, 1024, words * 4, s>>>(p, b);
-            const hipError_t err = hipGetLastError();
-            if (err == hipSuccess) return err;
-            lds_refused();   // not launched: the split form below
-        }
-    }
-    // else bin ranges per (event, layer): about one block per compute unit
-    const int nsplit = (int)std::max<size_t>(1, std::min<size_t>({(size_t)64, (nb + 63) / 64,
-                                                                  (size_t)(n_cu + blocks - 1) / blocks}));
-    const size_t chunk = ((nb + nsplit - 1) / nsplit + 63) / 64 * 64;
-    const bool fits = chunk * 4 <= lds || (chunk / 2 * 4 <= lds && b.max_layer_hits <= 0xFFFF);
-    if (fits) {
-        k_index_bin<<<grid, 256, 0, s>>>(p, b);
-        const hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-    }
-    if (fits && b.max_layer_hits <= 0xFFFF) {
-        k_index_range<true><<<blocks * nsplit, 1024, (chunk + 1) / 2 * 4, s>>>(p, b, nsplit, (int)chunk);
-        if (hipGetLastError() == hipSuccess) return hipSuccess;
-        lds_refused();   // not launched: try a smaller form
-    } else if (chunk * 4 <= lds) {
-        k_index_range<false><<<blocks * nsplit, 1024, chunk * 4, s>>>(p, b, nsplit, (int)chunk);
-        if (hipGetLastError() == hipSuccess) return hipSuccess;
-        lds_refused();
-    }
-    // bins beyond one block's LDS: device-wide counting atomics
-    k_index_prep<<<grid, 256, 0, s>>>(p, b);
+    const unsigned pairs = (unsigned)(b.n_events * p.n_layers);
+    // One block per (event, layer) or the bucketed build, whichever is sooner
+    // done.  Measured (us): a block takes 7 + 2.05 per 1,000 hits of the
+    // fullest layer (650 hits 9, 3,900 14, 13,000 29, 65,000 104); the three
+    // launches 14 + 0.0165 per 1,000 hits of the batch + 0.083 per (event,
+    // layer) pair for blocks that have little to do (one event of 6,500 hits a
+    // layer 17, of 13,000 19, of 65,000 31; 5, 7 and 10 events of 22,000 37,
+    // 45 and 58, where blocks take 50, 52 and 57; 64 of 1,300 84 against 27).
+    const double by_layer = 7.0 + 2.05e-3 * b.all.layer_hits;
+    const double bucketed = 14.0 + 1.65e-5 * b.total_hits + 0.083 * pairs;
+    if (b.layer_only.events == b.n_events || (by_layer < bucketed && layer_block_fits(b.all.layer_hits, b.all.bins)))
+        return launch_index_layer(p, b, b.all, 0, s);
+    const dim3 grid((unsigned)std::max(1, b.max_chunks), pairs);
+    k_index_hist<<<grid, kBlockThreads, 0, s>>>(p, b);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    k_index_scan<<<(unsigned)(b.n_events * p.n_layers), 1024, 0, s>>>(p, b);
+    k_index_part<<<grid, kBlockThreads, 0, s>>>(p, b);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    k_index_scatter<<<grid, 256, 0, s>>>(p, b);
-    return hipGetLastError();
+    k_index_place<<<dim3(kBuckets, pairs), kBlockThreads, sizeof(unsigned) << b.max_bucket_shift, s>>>(p, b);
+    err = hipGetLastError();
+    if (err != hipSuccess || b.layer_only.events == 0) return err;
+    return launch_index_layer(p, b, b.layer_only, 1, s);
 }
 
 size_t build_lds_bytes(int geo, int n_layers, int wpb)

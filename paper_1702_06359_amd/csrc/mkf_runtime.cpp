@@ -140,7 +140,6 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     if (input_end) *input_end = c.off;
     v->binned = c.take<float4>(n);
     v->bin_of = c.take<int>(n);
-    v->bin_rank = c.take<int>(n);
     v->out_rec = c.take<float>(kRecWords * ns);
     v->out_hits = c.take<int>(nl * ns);
     v->fit_rec = c.take<float>(kRecWords * nt);
@@ -151,11 +150,42 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     return c.off;
 }
 
-size_t carve_index(const EventShape &s, int nb, void *base, DevEvent *v)
+// Bytes of the working arrays of the bucketed index build (k_index_hist ff.);
+// 0, none, for an event that the one-block-per-layer build can index too (its
+// counters fit a block's LDS) when they exceed `allowance`.
+size_t index_work_bytes(const EventShape &s, int nb, size_t allowance, int *chunk, int *chunks)
+{
+    const int most = max_layer_hits(s);
+    *chunk = idx_chunk_of(most);
+    *chunks = (most + *chunk - 1) / *chunk;
+    const size_t need = (sizeof(float4) + sizeof(int)) * (size_t)s.n_hits() +
+                        sizeof(int) * (size_t)s.n_layers * ((size_t)*chunks * kBuckets + kBuckets + 1) + 4 * 256;
+    return need <= allowance || !layer_block_fits(most, nb) ? need : 0;
+}
+
+// What the budget of a served event allows it beyond its inputs, FP32 result rows, binned
+// hits and bin offsets: its results counted in the caller's types (the FP64
+// fields make 27 words more a row for the build's, 26 for a final fit's), an
+// int per hit and one per bin.
+size_t index_allowance(const EventShape &s, int nb)
+{
+    return sizeof(int) * ((27 + 26) * (size_t)s.n_seeds + (size_t)s.n_hits() + (size_t)s.n_layers * nb);
+}
+
+size_t carve_index(const EventShape &s, int nb, bool served, void *base, DevEvent *v)
 {
     Carver c(base);
-    v->bin_count = c.take<int>((size_t)s.n_layers * nb);
-    v->bin_off = c.take<int>((size_t)s.n_layers * bin_off_stride(nb));
+    const size_t nl = (size_t)s.n_layers, n = (size_t)s.n_hits();
+    v->bin_off = c.take<int>(nl * bin_off_stride(nb));
+    v->part = nullptr;
+    const size_t allow = served ? index_allowance(s, nb) : SIZE_MAX;
+    if (index_work_bytes(s, nb, allow, &v->idx_chunk, &v->idx_chunks)) {
+        v->bucket_shift = bucket_shift_of(nb);
+        v->part = c.take<float4>(n);
+        v->part_bin = c.take<int>(n);
+        v->hist = c.take<int>(nl * v->idx_chunks * kBuckets);
+        v->bucket_off = c.take<int>(nl * (kBuckets + 1));
+    }
     return c.off;
 }
 
@@ -560,10 +590,12 @@ size_t event_input_bytes(const EventShape &s)
     return end;
 }
 
-size_t event_index_bytes(const EventShape &s, int nb)
+size_t event_budget_bytes(const EventShape &s, int nb)
 {
-    DevEvent v{};
-    return carve_index(s, nb, nullptr, &v);
+    int chunk, chunks;
+    const size_t allow = index_allowance(s, nb), work = index_work_bytes(s, nb, allow, &chunk, &chunks);
+    const size_t off = sizeof(int) * (size_t)s.n_layers * bin_off_stride(nb);
+    return round_up_256(event_data_bytes(s)) + round_up_256(off) + round_up_256(std::max(allow, work));
 }
 
 size_t batch_scratch_bytes(int n)
@@ -822,16 +854,16 @@ mkf_status ensure_index_grid(mkf_ctx *ctx, EventRec *rec, int bp, int bz, bool *
     // the event's own grid: the context's, coarsened for a small event
     const int k = event_grid_shift(max_layer_hits(rec->shape), bp, bz);
     const int nb = (bp >> k) * (bz >> k);
-    const size_t bytes = event_index_bytes(rec->shape, nb);
+    const bool served = rec->heap != &ctx->heap;   // in the budget's slab
+    DevEvent sized{};
+    const size_t bytes = carve_index(rec->shape, nb, served, nullptr, &sized);
     rec->index = rec->heap->alloc(bytes);
     if (!rec->index) {
         rec->index_bins_phi = rec->index_bins_z = 0;
         return fail(MKF_E_NOMEM, "hit index: %zu bytes", bytes);
     }
-    carve_index(rec->shape, nb, rec->index, &rec->view);
+    carve_index(rec->shape, nb, served, rec->index, &rec->view);
     rec->view.grid_k = k;
-    // the index build expects zero bin counts (and leaves them at zero)
-    MKF_HIP(launch_fill_i32(rec->view.bin_count, 0, rec->shape.n_layers * nb, s));
     rec->index_bins_phi = bp;
     rec->index_bins_z = bz;
     drop_plain_graph(rec);
@@ -865,12 +897,19 @@ mkf_status compose_batch(EventRec *const *recs, int n, int spi, bool beam, char 
     int *tp = reinterpret_cast<int *>(h + o_trk);
     int *sp = reinterpret_cast<int *>(h + o_seed);
     long long items = 0, hits = 0, trks = 0, seeds = 0;
-    int max_layer = 0, max_bins = 0;
+    IndexExtent all{}, layer_only{};
+    int max_chunks = 0, max_shift = 0;
     for (int i = 0; i < n; ++i) {
         const EventShape &sh = recs[i]->shape;
-        for (int L = 0; L < sh.n_layers; ++L) max_layer = std::max(max_layer, sh.layer_off[L + 1] - sh.layer_off[L]);
         const int k = recs[i]->view.grid_k;
-        max_bins = std::max(max_bins, (recs[i]->index_bins_phi >> k) * (recs[i]->index_bins_z >> k));
+        const int bins = (recs[i]->index_bins_phi >> k) * (recs[i]->index_bins_z >> k);
+        all.add(max_layer_hits(sh), bins);
+        if (recs[i]->view.part) {
+            max_chunks = std::max(max_chunks, recs[i]->view.idx_chunks);
+            max_shift = std::max(max_shift, recs[i]->view.bucket_shift);
+        } else {
+            layer_only.add(max_layer_hits(sh), bins);
+        }
         ev[i] = recs[i]->view;
         if (beam) {   // this launch also writes every rank of the final beam
             const DevEvent &b = recs[i]->beam_view;
@@ -904,8 +943,10 @@ mkf_status compose_batch(EventRec *const *recs, int n, int spi, bool beam, char 
     args->total_tracks = (int)trks;
     args->total_seeds = (int)seeds;
     args->seeds_per_item = spi;
-    args->max_layer_hits = max_layer;
-    args->max_bins = max_bins;
+    args->all = all;
+    args->layer_only = layer_only;
+    args->max_chunks = max_chunks;
+    args->max_bucket_shift = max_shift;
     return MKF_OK;
 }
 
@@ -949,8 +990,6 @@ mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t,
                              uint32_t flags, bool timed, hipStream_t s)
 {
     const bool stats = flags & MKF_BATCH_STATS, reindex = flags & MKF_BATCH_REINDEX;
-    // bin counts are left at zero by every index build; fresh tables are
-    // cleared when they are allocated
     if (stats) MKF_HIP(launch_batch_zero(args, s));
     if (reindex) {
         if (timed) timer_begin(ctx, 1, s);

@@ -116,16 +116,9 @@ struct Server {
     PinnedPool pinned;
     std::thread thr;
 
-    // what one event takes of the budget: its data and its hit index, as the
-    // slab rounds them, the results of the build and of a final fit counted
-    // in the caller's types (FP64: 27 words more a row than their FP32 rows on
-    // the device for the build's, 26 for the fit's), so that a budget admits
-    // the same events whatever form the device keeps them in
     size_t footprint(const EventShape &s) const
     {
-        const size_t wide = round256((27 + 26) * sizeof(int) * (size_t)s.n_seeds);
-        return round256(event_data_bytes(s)) + wide +
-               round256(event_index_bytes(s, event_bins(s, tuning.bins_phi, tuning.bins_z)));
+        return event_budget_bytes(s, event_bins(s, tuning.bins_phi, tuning.bins_z));
     }
 
     void release_ticket_resources(Ticket *t)
