@@ -233,6 +233,7 @@ void *noalloc_scratch(int device);              // its device address (null befo
 // Launch helpers implemented in mkf_kernels.hip.
 size_t build_lds_bytes(int geo, int n_layers, int waves_per_block);   // dynamic LDS of a batched build block
 hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s);
+hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s);   // b may be null
 hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s);   // work counters of a batch
 hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s);
 hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int lanes_per_seed, int waves_per_block,

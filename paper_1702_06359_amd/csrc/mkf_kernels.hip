@@ -67,6 +67,15 @@ __global__ void k_fill_i32(int *__restrict__ p, int v, int n)
     if (i < n) p[i] = v;
 }
 
+// The device's wall clock (constant rate, one for the whole chip) at this
+// place of a stream, to one or two words of page-locked host memory.
+__global__ void k_stamp(unsigned long long *a, unsigned long long *b)
+{
+    const unsigned long long t = (unsigned long long)wall_clock64();
+    __hip_atomic_store(a, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (b) __hip_atomic_store(b, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Plain streaming copy used to calibrate memory-traffic counters.
 __global__ void k_copy16(const float4 *__restrict__ src, float4 *__restrict__ dst, size_t n)
 {
@@ -1896,6 +1905,12 @@ hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     k_fill_i32<<<blocks_for(n, 256), 256, 0, s>>>(ptr, value, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s)
+{
+    k_stamp<<<1, 1, 0, s>>>(a, b);
     return hipGetLastError();
 }
 

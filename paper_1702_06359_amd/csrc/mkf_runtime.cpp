@@ -450,38 +450,64 @@ mkf_status check_tuning(const mkf_config &c, mkf_tuning *t)
 
 void timers_collect(mkf_ctx *ctx, bool wait);
 
-void timer_begin(mkf_ctx *ctx, int which, hipStream_t s)
+// Opens an interval; returns where its start stamp goes (null: not timed).
+unsigned long long *timer_open(mkf_ctx *ctx, int which, hipStream_t s)
 {
     Timer &t = ctx->timers[which];
-    if (s != ctx->stream) return;
+    if (s != ctx->stream) return nullptr;
     if (t.count == Timer::kRing) timers_collect(ctx, true);
-    (void)hipEventRecord(t.start[(t.head + t.count) % Timer::kRing], s);
+    const int slot = (t.head + t.count) % Timer::kRing;
+    t.start[slot] = t.stop[slot] = 0;
     t.open = true;
+    return t.start + slot;
+}
+
+unsigned long long *timer_close(mkf_ctx *ctx, int which, hipStream_t s, long long launches)
+{
+    Timer &t = ctx->timers[which];
+    if (s != ctx->stream || !t.open) return nullptr;
+    const int slot = (t.head + t.count) % Timer::kRing;
+    t.ring_launches[slot] = launches;
+    ++t.count;
+    t.open = false;
+    return t.stop + slot;
+}
+
+void timer_begin(mkf_ctx *ctx, int which, hipStream_t s)
+{
+    if (unsigned long long *a = timer_open(ctx, which, s)) (void)launch_stamp(a, nullptr, s);
 }
 
 void timer_end(mkf_ctx *ctx, int which, hipStream_t s, long long launches)
 {
-    Timer &t = ctx->timers[which];
-    if (s != ctx->stream || !t.open) return;
-    const int slot = (t.head + t.count) % Timer::kRing;
-    (void)hipEventRecord(t.stop[slot], s);
-    t.ring_launches[slot] = launches;
-    ++t.count;
-    t.open = false;
+    if (unsigned long long *a = timer_close(ctx, which, s, launches)) (void)launch_stamp(a, nullptr, s);
+}
+
+// one phase ends, another begins
+void timer_switch(mkf_ctx *ctx, int from, int to, hipStream_t s, long long launches)
+{
+    unsigned long long *b = timer_open(ctx, to, s);   // first: it may collect
+    unsigned long long *a = timer_close(ctx, from, s, launches);
+    if (a && b) (void)launch_stamp(a, b, s);
 }
 
 // Adds the recorded intervals to the totals: all of them (waiting for the
 // device) or only those already complete.
 void timers_collect(mkf_ctx *ctx, bool wait)
 {
+    bool waited = false;
     for (auto &t : ctx->timers) {
         while (t.count > 0) {
             const int slot = t.head;
-            if (wait) (void)hipEventSynchronize(t.stop[slot]);
-            else if (hipEventQuery(t.stop[slot]) != hipSuccess) break;
-            float ms = 0.f;
-            if (hipEventElapsedTime(&ms, t.start[slot], t.stop[slot]) == hipSuccess) {
-                t.total_ms += ms;
+            if (wait && !waited) {
+                (void)hipStreamSynchronize(ctx->stream);
+                waited = true;
+            }
+            const unsigned long long a = __atomic_load_n(t.start + slot, __ATOMIC_RELAXED);
+            const unsigned long long b = __atomic_load_n(t.stop + slot, __ATOMIC_RELAXED);
+            if (b == 0 && !wait) break;
+            if (a != 0 && b > a) {
+                t.total_ms += (double)(b - a) * ctx->ms_per_tick;
                 t.launches += t.ring_launches[slot];
             }
             t.head = (t.head + 1) % Timer::kRing;
@@ -994,17 +1020,18 @@ mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t,
     if (reindex) {
         if (timed) timer_begin(ctx, 1, s);
         MKF_HIP(launch_index(P, args, s));
-        if (timed) timer_end(ctx, 1, s, 1);   // one index build of the batch
     }
     if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
-    if (timed) timer_begin(ctx, 0, s);
+    if (timed && reindex) timer_switch(ctx, 1, 0, s, 1);   // one index build of the batch
+    else if (timed) timer_begin(ctx, 0, s);
     MKF_HIP(launch_build_batch(P, args, t.lanes_per_seed, t.waves_per_block, t.persistent,
                                ctx->n_cu * t.blocks_per_cu, stats, s));
-    if (timed) timer_end(ctx, 0, s, 1);
     if (flags & MKF_BATCH_FIT) {
-        if (timed) timer_begin(ctx, 2, s);
+        if (timed) timer_switch(ctx, 0, 2, s, 1);
         MKF_HIP(launch_refit(P, args, s));
         if (timed) timer_end(ctx, 2, s, 1);
+    } else if (timed) {
+        timer_end(ctx, 0, s, 1);
     }
     return MKF_OK;
 }
@@ -1303,11 +1330,16 @@ mkf_status mkf_create(const mkf_config *cfg, const mkf_allocator *alloc, void *h
     std::memset(&ctx->tuning, 0, sizeof(ctx->tuning));
     if ((st = check_tuning(ctx->cfg, &ctx->tuning)) != MKF_OK) return st;
     derive_params(ctx.get());
-    for (auto &t : ctx->timers)
-        for (int i = 0; i < Timer::kRing; ++i) {
-            MKF_HIP(hipEventCreate(&t.start[i]));
-            MKF_HIP(hipEventCreate(&t.stop[i]));
-        }
+    int khz = 0;
+    MKF_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+    if (khz <= 0) return fail(MKF_E_DEVICE, "device %d has no wall clock", dev);
+    ctx->ms_per_tick = 1.0 / khz;
+    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), 3 * 2 * Timer::kRing * sizeof(unsigned long long),
+                          hipHostMallocDefault));
+    for (int k = 0; k < 3; ++k) {
+        ctx->timers[k].start = ctx->stamps + (2 * k) * Timer::kRing;
+        ctx->timers[k].stop = ctx->stamps + (2 * k + 1) * Timer::kRing;
+    }
     MKF_HIP(hipEventCreateWithFlags(&ctx->stage_done, hipEventDisableTiming));
     // device address of this GPU's fixed batch-descriptor array (the
     // no-allocation builder); looked up once per device
@@ -1329,11 +1361,7 @@ void mkf_destroy(mkf_ctx *ctx)
     if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
     for (hipEvent_t e : ctx->out_done)
         if (e) (void)hipEventDestroy(e);
-    for (auto &t : ctx->timers)
-        for (int i = 0; i < Timer::kRing; ++i) {
-            if (t.start[i]) (void)hipEventDestroy(t.start[i]);
-            if (t.stop[i]) (void)hipEventDestroy(t.stop[i]);
-        }
+    if (ctx->stamps) (void)hipHostFree(ctx->stamps);
     if (ctx->stage_done) (void)hipEventDestroy(ctx->stage_done);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

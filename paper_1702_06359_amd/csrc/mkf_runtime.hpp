@@ -104,12 +104,15 @@ struct BatchGraph {
     hipGraphExec_t exec = nullptr;
 };
 
-// Device time of the timed phases: a ring of event pairs, so that calls
-// that return before the device finishes (asynchronous batches) each keep
-// their own interval until it is collected.
+// Device time of the timed phases: a ring of (start, stop) wall-clock stamps
+// in page-locked memory, so that calls that return before the device finishes
+// (asynchronous batches) each keep their own interval until it is collected.
+// The stamps are written by a one-thread kernel in the stream: 1.5 us each,
+// where a pair of HIP events around a kernel adds 5.6-6.5 us to a call.  A
+// phase that ends where the next begins shares its stamp.
 struct Timer {
     static constexpr int kRing = 32;
-    hipEvent_t start[kRing] = {}, stop[kRing] = {};
+    unsigned long long *start = nullptr, *stop = nullptr;   // kRing each; 0: not written yet
     long long ring_launches[kRing] = {};
     int head = 0, count = 0;   // recorded intervals not yet collected
     bool open = false;         // between timer_begin and timer_end
@@ -182,6 +185,8 @@ struct mkf_ctx {
     hipEvent_t out_done[mkf::kOutSlots] = {};   // a slot of the result staging filled by the device
     std::vector<std::unique_ptr<mkf::BatchGraph>> graphs;
     mkf::Timer timers[3];
+    unsigned long long *stamps = nullptr;       // their rings, page-locked
+    double ms_per_tick = 0.0;
     std::unique_ptr<mkf::Server, mkf::ServerDeleter> server;
 };
 
