@@ -13,8 +13,8 @@ LIB = os.path.join(HERE, "libmkf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["mkf_kernels.hip", "mkf_runtime.cpp", "mkf_serve.cpp"]
-HEADERS = ["mkf_internal.hpp", "mkf_device.hpp", "mkf_runtime.hpp"]
+SOURCES = ["mkf_kernels.hip", "mkf_runtime.cpp", "mkf_serve.cpp", "mkf_pack.cpp"]
+HEADERS = ["mkf_internal.hpp", "mkf_device.hpp", "mkf_runtime.hpp", "mkf_pack.hpp"]
 
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
@@ -24,10 +24,17 @@ FLAGS = [
 ]
 
 
+# host packing: plain C++, vectorised, without fused multiply-adds (every
+# vector width rounds alike)
+PACK_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-math-errno", "-fno-trapping-math", "-Wall"]
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-    if src.endswith(".cpp"):
+    if src == "mkf_pack.cpp":
+        cmd = [HIPCC, "-xc++", *PACK_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    elif src.endswith(".cpp"):
         cmd.insert(1, "-xhip")
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

@@ -1,6 +1,8 @@
 // Host runtime and C ABI of the track builder (everything except serving).
 #include "mkf_runtime.hpp"
 
+#include "mkf_pack.hpp"
+
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -123,8 +125,9 @@ struct Carver {
     }
 };
 
-// The event's inputs come first (hits, seeds, tracks, as the host packs
-// them: one copy moves them all), then the index, outputs and descriptor.
+// The event's inputs come first (hits, seeds, tracks as the host packs them,
+// cleared work counters and the descriptor: one copy moves them all), then
+// the binned hits and the results.
 size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_view, size_t *input_end = nullptr)
 {
     Carver c(base);
@@ -137,6 +140,9 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     v->track_par = c.take<float>(6 * nt);
     v->track_cov = c.take<float>(21 * nt);
     v->track_hits = c.take<int>(nl * nt);
+    v->stats = c.take<unsigned long long>(5);
+    DevEvent *dv = c.take<DevEvent>(1);
+    if (dev_view) *dev_view = dv;
     if (input_end) *input_end = c.off;
     v->binned = c.take<float4>(n);
     v->bin_of = c.take<int>(n);
@@ -144,9 +150,6 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     v->out_hits = c.take<int>(nl * ns);
     v->fit_rec = c.take<float>(kRecWords * nt);
     v->rf_rec = c.take<float>(kRecWords * ns);
-    v->stats = c.take<unsigned long long>(5);
-    DevEvent *dv = c.take<DevEvent>(1);
-    if (dev_view) *dev_view = dv;
     return c.off;
 }
 
@@ -207,25 +210,6 @@ size_t carve_plain(const EventShape &s, int slots, void *base, DevEvent *v)
     v->st_hist = c.take<int>((size_t)s.n_layers * S);
     v->st_slots = slots;
     return c.off;
-}
-
-bool finite_all(const double *p, size_t n)
-{
-    for (size_t i = 0; i < n; ++i)
-        if (!std::isfinite(p[i])) return false;
-    return true;
-}
-
-// FP64 -> FP32 with the check that the value is, and stays, finite.
-bool narrow(const double *src, float *dst, size_t n)
-{
-    bool ok = true;
-    for (size_t i = 0; i < n; ++i) {
-        const float f = (float)src[i];
-        dst[i] = f;
-        ok &= std::isfinite(f);
-    }
-    return ok;
 }
 
 // Host threads that pack inputs, started on first use and kept for the life
@@ -601,11 +585,22 @@ size_t event_data_bytes(const EventShape &s)
     return carve_data(s, nullptr, &v, nullptr);
 }
 
-int pack_threads(size_t n_values)
+int pack_threads(size_t n_values, size_t per_thread)
 {
-    // a thread per ~100k values of FP64 input, up to 16
     const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-    return (int)std::min<size_t>({(size_t)16, (size_t)hw, 1 + n_values / 100000});
+    return (int)std::min<size_t>({(size_t)16, (size_t)hw, 1 + n_values / per_thread});
+}
+
+// the hits, at the front of the inputs, up to where the seeds begin
+size_t event_hit_bytes(const EventShape &s) { return round_up_256(sizeof(float4) * (size_t)s.n_hits()); }
+
+size_t event_view_offset(const EventShape &s)
+{
+    DevEvent v{};
+    DevEvent *dv = nullptr;
+    char origin = 0;   // only offsets from it are taken
+    carve_data(s, &origin, &v, &dv);
+    return reinterpret_cast<char *>(dv) - &origin;
 }
 
 size_t event_input_bytes(const EventShape &s)
@@ -668,22 +663,35 @@ mkf_status validate_event(const mkf_ctx *ctx, const mkf_event *ev, EventShape *s
     return MKF_OK;
 }
 
-// Checks a state (finite, theta in (0, pi), off the axis) and the hit
-// indices of one seed or track; writes its FP32 state and covariance.
-static bool pack_state(const double *par, const double *cov, float *fpar, float *fcov, const int32_t *hits,
-                       int32_t *ohits, int n_hit_layers, const int32_t *n_hits, int *bad_hit)
+// Writes the FP32 states, covariances and hit indices of n seeds or tracks
+// (n_hit_layers indices a row) and checks them: finite, theta in (0, pi), off
+// the axis, indices in range.  -1, or the first row that fails, *bad_hit set
+// when by a hit index.
+static long long pack_states(const double *par, const double *cov, const int32_t *hits, size_t n, int n_hit_layers,
+                             const int32_t *n_hits, float *fpar, float *fcov, int *ohits, int *bad_hit)
 {
-    if (!narrow(par, fpar, 6) || !narrow(cov, fcov, 21)) return false;
-    if (!(par[5] > 0 && par[5] < M_PI) || !(par[0] * par[0] + par[1] * par[1] > 0)) return false;
-    for (int L = 0; L < n_hit_layers; ++L) {
-        const int32_t h = hits[L];
-        if (h < -1 || h >= n_hits[L]) {
-            *bad_hit = 1;
-            return false;
+    bool ok = narrow_all(par, fpar, 6 * n) & narrow_all(cov, fcov, 21 * n) & states_in_range(par, n);
+    int out = 0;
+    for (size_t i = 0; i < n; ++i)
+        for (int L = 0; L < n_hit_layers; ++L) {
+            const int32_t h = hits[i * n_hit_layers + L];
+            out |= (h < -1) | (h >= n_hits[L]);
+            ohits[i * n_hit_layers + L] = h;
         }
-        ohits[L] = h;
+    if (ok && !out) return -1;
+    for (size_t i = 0; i < n; ++i) {
+        if (!narrow_all(par + 6 * i, fpar + 6 * i, 6) || !narrow_all(cov + 21 * i, fcov + 21 * i, 21) ||
+            !states_in_range(par + 6 * i, 1))
+            return (long long)i;
+        for (int L = 0; L < n_hit_layers; ++L) {
+            const int32_t h = hits[i * n_hit_layers + L];
+            if (h < -1 || h >= n_hits[L]) {
+                *bad_hit = 1;
+                return (long long)i;
+            }
+        }
     }
-    return true;
+    return -1;
 }
 
 // Packs an event's inputs into `image` in the device layout of its data
@@ -714,65 +722,55 @@ static void order_seeds(const std::vector<uint16_t> &sector, int *order)
     for (int i = 0; i < (int)sector.size(); ++i) order[start[sector[i]]++] = i;
 }
 
-mkf_status pack_event(const mkf_event *ev, const EventShape &sh, int geo, void *image, int threads, std::string *why)
+mkf_status pack_event(const mkf_event *ev, const EventShape &sh, int geo, void *image, int threads, std::string *why,
+                      PackPart part)
 {
     DevEvent v{};
     carve_data(sh, image, &v, nullptr);
-    const int nl = sh.n_layers, nsl = sh.n_seed_layers;
+    const int nsl = sh.n_seed_layers;
+    const int nl = part == PackPart::kRows ? 0 : sh.n_layers;   // layers packed by this call
+    const bool rows = part != PackPart::kHits;
     const int chunk = 4096;
-    const int seed_tasks = (sh.n_seeds + chunk - 1) / chunk, track_tasks = (sh.n_tracks + chunk - 1) / chunk;
+    const int seed_tasks = rows ? (sh.n_seeds + chunk - 1) / chunk : 0;
+    const int track_tasks = rows ? (sh.n_tracks + chunk - 1) / chunk : 0;
     const int n_tasks = nl + seed_tasks + track_tasks;
+    if (rows) std::memset(v.stats, 0, 5 * sizeof(*v.stats));
+    const HitForm form = geo & 2 ? HitForm::kXyz : geo & 1 ? HitForm::kDisk : HitForm::kCylinder;
     // first failure of each task: (index, kind), index -1 for none
     std::vector<int> bad(n_tasks, -1), kind(n_tasks, 0);
-    std::vector<uint16_t> sector(sh.n_seeds);   // azimuth sector of each seed, taken while it is packed
+    std::vector<uint16_t> sector(rows ? sh.n_seeds : 0);   // azimuth sector of each seed, taken while it is packed
     run_tasks(n_tasks, threads, [&](int t) {
         if (t < nl) {
             // a hit as the kernels read it: its direction and second grid
             // coordinate computed here in FP64 and rounded once
-            const int n = ev->n_hits[t];
-            const double *h = ev->hit_xyz[t];
-            float4 *o = const_cast<float4 *>(v.hits) + sh.layer_off[t];
-            const bool xyz = (geo & 2) != 0, disk = (geo & 1) != 0;
-            for (int i = 0; i < n; ++i) {
-                const double x = h[3 * i], y = h[3 * i + 1], z = h[3 * i + 2];
-                const double r = std::sqrt(x * x + y * y);
-                float4 f;
-                if (xyz) f = make_float4((float)x, (float)y, (float)z, 0.f);
-                else if (disk) f = make_float4((float)(x / r), (float)(y / r), (float)r, (float)z);
-                else f = make_float4((float)(x / r), (float)(y / r), (float)z, (float)r);
-                o[i] = f;
-                if (!(r > 0) || !std::isfinite(f.x) || !std::isfinite(f.y) || !std::isfinite(f.z) ||
-                    !std::isfinite(f.w) || (xyz && !((double)f.x * f.x + (double)f.y * f.y > 0))) {
-                    bad[t] = i;
+            const size_t n = (size_t)ev->n_hits[t];
+            float *o = reinterpret_cast<float *>(const_cast<float4 *>(v.hits) + sh.layer_off[t]);
+            if (pack_hits(ev->hit_xyz[t], n, form, o)) return;
+            for (size_t i = 0; i < n; ++i)   // the first that failed
+                if (!pack_hits(ev->hit_xyz[t] + 3 * i, 1, form, o + 4 * i)) {
+                    bad[t] = (int)i;
                     return;
                 }
-            }
-            return;
         }
         const bool seeds = t < nl + seed_tasks;
-        const int i0 = (seeds ? t - nl : t - nl - seed_tasks) * chunk;
-        const int i1 = std::min(i0 + chunk, seeds ? sh.n_seeds : sh.n_tracks);
-        for (int i = i0; i < i1; ++i) {
-            int bad_hit = 0;
-            const bool ok = seeds ? pack_state(ev->seed_par + 6 * (size_t)i, ev->seed_cov + 21 * (size_t)i,
-                                               const_cast<float *>(v.seed_par) + 6 * (size_t)i,
-                                               const_cast<float *>(v.seed_cov) + 21 * (size_t)i,
-                                               ev->seed_hits + (size_t)i * nsl,
-                                               const_cast<int *>(v.seed_hits) + (size_t)i * nsl, nsl, ev->n_hits,
-                                               &bad_hit)
-                                  : pack_state(ev->track_par + 6 * (size_t)i, ev->track_cov + 21 * (size_t)i,
-                                               const_cast<float *>(v.track_par) + 6 * (size_t)i,
-                                               const_cast<float *>(v.track_cov) + 21 * (size_t)i,
-                                               ev->track_hits + (size_t)i * nl,
-                                               const_cast<int *>(v.track_hits) + (size_t)i * nl, nl, ev->n_hits,
-                                               &bad_hit);
-            if (!ok) {
-                bad[t] = i;
-                kind[t] = bad_hit;
-                return;
-            }
-            if (seeds) sector[i] = seed_sector(ev->seed_par[6 * (size_t)i + 4]);
+        const size_t i0 = (size_t)(seeds ? t - nl : t - nl - seed_tasks) * chunk;
+        const size_t n = std::min<size_t>(chunk, (seeds ? sh.n_seeds : sh.n_tracks) - i0);
+        const int nh = seeds ? nsl : sh.n_layers;   // hit indices of a row
+        const double *par = (seeds ? ev->seed_par : ev->track_par) + 6 * i0;
+        const double *cov = (seeds ? ev->seed_cov : ev->track_cov) + 21 * i0;
+        const int32_t *hits = (seeds ? ev->seed_hits : ev->track_hits) + nh * i0;
+        float *fpar = const_cast<float *>(seeds ? v.seed_par : v.track_par) + 6 * i0;
+        float *fcov = const_cast<float *>(seeds ? v.seed_cov : v.track_cov) + 21 * i0;
+        int *ohits = const_cast<int *>(seeds ? v.seed_hits : v.track_hits) + nh * i0;
+        int bad_hit = 0;
+        const long long failed = pack_states(par, cov, hits, n, nh, ev->n_hits, fpar, fcov, ohits, &bad_hit);
+        if (failed >= 0) {
+            bad[t] = (int)(i0 + failed);
+            kind[t] = bad_hit;
+            return;
         }
+        if (seeds)
+            for (size_t i = 0; i < n; ++i) sector[i0 + i] = seed_sector(par[6 * i + 4]);
     });
     for (int t = 0; t < n_tasks; ++t) {
         if (bad[t] < 0) continue;
@@ -788,7 +786,7 @@ mkf_status pack_event(const mkf_event *ev, const EventShape &sh, int geo, void *
         *why = msg;
         return MKF_E_INVALID;
     }
-    order_seeds(sector, const_cast<int *>(v.seed_order));
+    if (rows) order_seeds(sector, const_cast<int *>(v.seed_order));
     return MKF_OK;
 }
 
@@ -813,11 +811,12 @@ mkf_status create_event(mkf_ctx *ctx, const EventShape &shape, DeviceHeap *heap,
     return MKF_OK;
 }
 
-// Copies an event's packed inputs (pack_event) into its device data block.
-mkf_status upload_packed(EventRec *rec, const void *image, hipStream_t s)
+// Copies an event's packed inputs (pack_event) and its descriptor, now that
+// its addresses are known, into its device data block.
+mkf_status upload_packed(EventRec *rec, void *image, hipStream_t s)
 {
-    const size_t bytes = event_input_bytes(rec->shape);
-    if (bytes) MKF_HIP(hipMemcpyAsync(rec->data, image, bytes, hipMemcpyHostToDevice, s));
+    std::memcpy(static_cast<char *>(image) + event_view_offset(rec->shape), &rec->view, sizeof(DevEvent));
+    MKF_HIP(hipMemcpyAsync(rec->data, image, event_input_bytes(rec->shape), hipMemcpyHostToDevice, s));
     return MKF_OK;
 }
 
@@ -1420,38 +1419,46 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
     };
     hipStream_t s = ctx->stream;
     // device memory first (the allocator may call back into the caller, so
-    // on this thread); then every event is packed and its copy queued as soon
-    // as its packing ends, so that the copies overlap the packing of the
-    // others
-    for (int i = 0; i < n; ++i)
+    // on this thread)
+    for (int i = 0; i < n; ++i) {
+        bool rebuilt = false;
         if ((st = create_event(ctx, shapes[i], &ctx->heap, &recs[i])) != MKF_OK) return undo(st);
+        if ((st = ensure_index(ctx, recs[i].get(), &rebuilt, s)) != MKF_OK) return undo(st);
+    }
+    // the hits of every event, then the index, then the seeds and tracks: a
+    // part's copy is queued as soon as it is packed, so that the copies and the
+    // index overlap the packing of what follows
     std::vector<mkf_status> sts(n, MKF_OK);
     std::vector<std::string> why(n);
     std::vector<hipError_t> copied(n, hipSuccess);
-    auto pack_send = [&](int i, int th) {
-        sts[i] = pack_event(&evs[i], shapes[i], ctx->params.geo, pin + off[i], th, &why[i]);
-        const size_t bytes = event_input_bytes(shapes[i]);
-        if (sts[i] == MKF_OK && bytes)
-            copied[i] = hipMemcpyAsync(recs[i]->data, pin + off[i], bytes, hipMemcpyHostToDevice, s);
+    const int threads = pack_threads(values, kLoadValuesPerThread);
+    auto pack_send = [&](PackPart part) -> mkf_status {
+        run_tasks(n, n == 1 ? 1 : threads, [&](int i) {
+            char *image = pin + off[i];
+            sts[i] = pack_event(&evs[i], shapes[i], ctx->params.geo, image, n == 1 ? threads : 1, &why[i], part);
+            if (sts[i] != MKF_OK) return;
+            const size_t hits = event_hit_bytes(shapes[i]);
+            const size_t from = part == PackPart::kRows ? hits : 0;
+            const size_t bytes = (part == PackPart::kHits ? hits : event_input_bytes(shapes[i])) - from;
+            if (part != PackPart::kHits)
+                std::memcpy(image + event_view_offset(shapes[i]), &recs[i]->view, sizeof(DevEvent));
+            if (bytes)
+                copied[i] = hipMemcpyAsync(static_cast<char *>(recs[i]->data) + from, image + from, bytes,
+                                           hipMemcpyHostToDevice, s);
+        });
+        for (int i = 0; i < n; ++i)
+            if (sts[i] != MKF_OK)
+                return n == 1 ? fail(sts[i], "%s", why[i].c_str()) : fail(sts[i], "event %d: %s", i, why[i].c_str());
+        for (int i = 0; i < n; ++i)
+            if (copied[i] != hipSuccess) {
+                note_device_error(copied[i]);
+                return fail(MKF_E_DEVICE, "load: %s", hipGetErrorString(copied[i]));
+            }
+        return MKF_OK;
     };
-    const int threads = pack_threads(values);
-    if (n == 1) pack_send(0, threads);
-    else run_tasks(n, threads, [&](int i) { pack_send(i, 1); });
-    for (int i = 0; i < n; ++i)
-        if (sts[i] != MKF_OK) return undo(n == 1 ? fail(sts[i], "%s", why[i].c_str())
-                                                 : fail(sts[i], "event %d: %s", i, why[i].c_str()));
-    for (int i = 0; i < n; ++i)
-        if (copied[i] != hipSuccess) {
-            note_device_error(copied[i]);
-            return undo(fail(MKF_E_DEVICE, "load: %s", hipGetErrorString(copied[i])));
-        }
-    for (int i = 0; i < n; ++i) {
-        bool rebuilt = false;
-        if ((st = ensure_index(ctx, recs[i].get(), &rebuilt, s)) != MKF_OK) return undo(st);
-        const hipError_t e = hipMemcpyAsync(recs[i]->dev_view, &recs[i]->view, sizeof(DevEvent),
-                                            hipMemcpyHostToDevice, s);
-        if (e != hipSuccess) return undo(fail(MKF_E_DEVICE, "load: %s", hipGetErrorString(e)));
-    }
+    // (small inputs in one part: a second copy takes longer than it hides)
+    const bool two = off[n] >= (512u << 10);
+    if ((st = pack_send(two ? PackPart::kHits : PackPart::kAll)) != MKF_OK) return undo(st);
     if ((st = ensure_batch_scratch(ctx, n)) != MKF_OK) return undo(st);
     std::vector<EventRec *> raw(n);
     for (int i = 0; i < n; ++i) raw[i] = recs[i].get();
@@ -1459,9 +1466,11 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
     if ((st = stage_batch(ctx, raw, ctx->batch_dev, ctx->batch_host, seeds_per_item(ctx->tuning.lanes_per_seed),
                           &args, s)) != MKF_OK)
         return undo(st);
-    hipError_t e = launch_batch_zero(args, s);
-    if (e == hipSuccess) e = launch_index(ctx->params, args, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    hipError_t e = launch_index(ctx->params, args, s);
+    if (e == hipSuccess) {
+        if (two && (st = pack_send(PackPart::kRows)) != MKF_OK) return undo(st);
+        e = hipStreamSynchronize(s);
+    }
     if (e != hipSuccess) {
         note_device_error(e);
         return undo(fail(MKF_E_DEVICE, "load: %s", hipGetErrorString(e)));
@@ -1874,15 +1883,14 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     layout(static_cast<char *>(ctx->load_pin), &hv);
     std::vector<int32_t> nh(nl);
     for (size_t L = 0; L < nl; ++L) nh[L] = rec->shape.layer_off[L + 1] - rec->shape.layer_off[L];
-    for (int i = 0; i < n_tracks; ++i) {
-        int bad_hit = 0;
-        if (!pack_state(init_par + 6 * (size_t)i, init_cov + 21 * (size_t)i, const_cast<float *>(hv.track_par) + 6 * (size_t)i,
-                        const_cast<float *>(hv.track_cov) + 21 * (size_t)i, track_hits + (size_t)i * nl,
-                        const_cast<int *>(hv.track_hits) + (size_t)i * nl, (int)nl, nh.data(), &bad_hit))
-            return fail(MKF_E_INVALID, bad_hit ? "track %d: hit index out of range"
-                                               : "track %d: state or covariance not finite (in FP32), theta "
-                                                 "outside (0, pi) or position on the axis", i);
-    }
+    int bad_hit = 0;
+    const long long failed = pack_states(init_par, init_cov, track_hits, nt, (int)nl, nh.data(),
+                                         const_cast<float *>(hv.track_par), const_cast<float *>(hv.track_cov),
+                                         const_cast<int *>(hv.track_hits), &bad_hit);
+    if (failed >= 0)
+        return fail(MKF_E_INVALID, bad_hit ? "track %d: hit index out of range"
+                                           : "track %d: state or covariance not finite (in FP32), theta "
+                                             "outside (0, pi) or position on the axis", (int)failed);
     char *buf = static_cast<char *>(ctx->heap.alloc(sizes.second + sizeof(DevEvent) + 256));
     if (!buf) return fail(MKF_E_NOMEM, "fit buffers: %zu bytes", sizes.second);
     DevEvent v = rec->view;

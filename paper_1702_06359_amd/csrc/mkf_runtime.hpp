@@ -197,11 +197,19 @@ namespace mkf {
 mkf_status validate_event(const mkf_ctx *ctx, const mkf_event *ev, EventShape *shape);
 // the event's inputs, checked and narrowed to FP32, in its device layout
 // (event_input_bytes of them)
+enum class PackPart { kAll, kHits, kRows };   // all inputs, the hits alone, the seeds and tracks
 mkf_status pack_event(const mkf_event *ev, const EventShape &shape, int geo, void *image, int threads,
-                      std::string *why);
-int pack_threads(size_t n_values);   // host threads worth using for packing that many values
+                      std::string *why, PackPart part = PackPart::kAll);
+// Host threads worth using for packing that many FP64 values, up to 16.  One
+// packs 3 to 4.5 values a nanosecond, and waking others takes 30 to 50 us: a
+// load of 7,001 seeds (460,000 values) takes 102 us to pack on one thread, 131
+// on two, 117 on eight.  A submit to the server, whose staging is colder, packs
+// 717,000 values in 151 us on one thread, 142 on two, 116 on four.
+constexpr size_t kLoadValuesPerThread = 1500000, kServeValuesPerThread = 400000;
+int pack_threads(size_t n_values, size_t per_thread);
 mkf_status create_event(mkf_ctx *ctx, const EventShape &shape, DeviceHeap *heap, std::unique_ptr<EventRec> *out);
-mkf_status upload_packed(EventRec *rec, const void *image, hipStream_t s);
+size_t event_view_offset(const EventShape &s);   // of the event's descriptor in its packed inputs
+mkf_status upload_packed(EventRec *rec, void *image, hipStream_t s);
 void destroy_event(mkf_ctx *ctx, EventRec *rec);
 mkf_status ensure_index(mkf_ctx *ctx, EventRec *rec, bool *rebuilt, hipStream_t s);
 mkf_status ensure_index_grid(mkf_ctx *ctx, EventRec *rec, int bins_phi, int bins_z, bool *rebuilt, hipStream_t s);

@@ -27,18 +27,25 @@ constexpr int kStreams = 4;
 
 size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Reuses pinned host buffers by power-of-two size class.
+// Reuses pinned host buffers by power-of-two size class.  A buffer is kept for
+// the use it had (inputs or results): an input buffer stays in the cache of the
+// threads that pack into it instead of coming back from the one that copies
+// results out (one submit of 10,900 seeds: 151 against 319 us).  Where its own
+// use has none free it takes one of the other's before making a new one.
 class PinnedPool {
   public:
-    void *get(size_t bytes, size_t *cls)
+    enum Use { kInput, kResult };
+
+    void *get(size_t bytes, Use use, size_t *cls)
     {
         size_t c = 4096;
         while (c < bytes) c <<= 1;
         *cls = c;
         {
             std::lock_guard<std::mutex> lk(mu_);
-            auto it = free_.find(c);
-            if (it != free_.end() && !it->second.empty()) {
+            for (int u : {(int)use, 1 - (int)use}) {
+                auto it = free_[u].find(c);
+                if (it == free_[u].end() || it->second.empty()) continue;
                 void *p = it->second.back();
                 it->second.pop_back();
                 return p;
@@ -48,21 +55,22 @@ class PinnedPool {
         if (hipHostMalloc(&p, c, hipHostMallocDefault) != hipSuccess) return nullptr;
         return p;
     }
-    void put(void *p, size_t cls)
+    void put(void *p, Use use, size_t cls)
     {
         if (!p) return;
         std::lock_guard<std::mutex> lk(mu_);
-        free_[cls].push_back(p);
+        free_[use][cls].push_back(p);
     }
     ~PinnedPool()
     {
-        for (auto &kv : free_)
-            for (void *p : kv.second) (void)hipHostFree(p);
+        for (auto &m : free_)
+            for (auto &kv : m)
+                for (void *p : kv.second) (void)hipHostFree(p);
     }
 
   private:
     std::mutex mu_;
-    std::map<size_t, std::vector<void *>> free_;
+    std::map<size_t, std::vector<void *>> free_[2];
 };
 
 struct Ticket {
@@ -125,8 +133,8 @@ struct Server {
     {
         if (t->rec) destroy_event(ctx, t->rec.get());
         t->rec.reset();
-        pinned.put(t->in_pin, t->in_cls);
-        pinned.put(t->out_pin, t->out_cls);
+        pinned.put(t->in_pin, PinnedPool::kInput, t->in_cls);
+        pinned.put(t->out_pin, PinnedPool::kResult, t->out_cls);
         t->in_pin = t->out_pin = nullptr;
     }
 
@@ -286,8 +294,8 @@ void shutdown_server(mkf_ctx *ctx)
         sv->stop = true;
         // tickets not started are abandoned
         for (Ticket *t : sv->admitted) {
-            sv->pinned.put(t->in_pin, t->in_cls);
-            sv->pinned.put(t->out_pin, t->out_cls);
+            sv->pinned.put(t->in_pin, PinnedPool::kInput, t->in_cls);
+            sv->pinned.put(t->out_pin, PinnedPool::kResult, t->out_cls);
             t->in_pin = t->out_pin = nullptr;
         }
         sv->admitted.clear();
@@ -408,11 +416,11 @@ mkf_status mkf_serve_submit(mkf_ctx *ctx, const mkf_event *ev, mkf_tracks *out, 
         stage_off[f] = staged;
         if (!t->dst[f]) staged += round256(bytes);
     }
-    t->in_pin = sv->pinned.get(event_input_bytes(shape), &t->in_cls);
-    if (staged) t->out_pin = sv->pinned.get(staged, &t->out_cls);
+    t->in_pin = sv->pinned.get(event_input_bytes(shape), PinnedPool::kInput, &t->in_cls);
+    if (staged) t->out_pin = sv->pinned.get(staged, PinnedPool::kResult, &t->out_cls);
     if (!t->in_pin || (staged && !t->out_pin)) {
-        sv->pinned.put(t->in_pin, t->in_cls);
-        sv->pinned.put(t->out_pin, t->out_cls);
+        sv->pinned.put(t->in_pin, PinnedPool::kInput, t->in_cls);
+        sv->pinned.put(t->out_pin, PinnedPool::kResult, t->out_cls);
         unreserve();
         return fail(MKF_E_NOMEM, "pinned staging");
     }
@@ -428,9 +436,9 @@ mkf_status mkf_serve_submit(mkf_ctx *ctx, const mkf_event *ev, mkf_tracks *out, 
     seeds_only.n_tracks = 0;   // serving builds; tracks for fitting are not staged
     std::string why;
     const size_t values = (size_t)shape.n_hits() * 3 + (size_t)shape.n_seeds * 27;
-    if ((st = pack_event(&seeds_only, shape, sv->params.geo, t->in_pin, pack_threads(values), &why)) != MKF_OK) {
-        sv->pinned.put(t->in_pin, t->in_cls);
-        sv->pinned.put(t->out_pin, t->out_cls);
+    if ((st = pack_event(&seeds_only, shape, sv->params.geo, t->in_pin, pack_threads(values, kServeValuesPerThread), &why)) != MKF_OK) {
+        sv->pinned.put(t->in_pin, PinnedPool::kInput, t->in_cls);
+        sv->pinned.put(t->out_pin, PinnedPool::kResult, t->out_cls);
         unreserve();
         return fail(st, "%s", why.c_str());
     }
@@ -472,8 +480,8 @@ mkf_status mkf_serve_cancel(mkf_ctx *ctx, uint64_t ticket)
     Ticket *t = it->second.get();
     if (t->state != 0) return fail(MKF_E_STATE, "ticket already started");
     sv->admitted.erase(std::find(sv->admitted.begin(), sv->admitted.end(), t));
-    sv->pinned.put(t->in_pin, t->in_cls);
-    sv->pinned.put(t->out_pin, t->out_cls);
+    sv->pinned.put(t->in_pin, PinnedPool::kInput, t->in_cls);
+    sv->pinned.put(t->out_pin, PinnedPool::kResult, t->out_cls);
     --sv->in_flight;
     sv->reserved -= t->reserved;
     sv->tickets.erase(it);
