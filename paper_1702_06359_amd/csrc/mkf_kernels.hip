@@ -1320,6 +1320,91 @@ __device__ __forceinline__ void flush_counts(const Count &cnt, CEvent &E, int la
     }
 }
 
+// LDS stride of a result row staged for 64 rows' contiguous way out: odd, so
+// that the lanes' own rows fall on different banks.
+constexpr int kRecLds = kRecWords + 1;
+
+// ---------------------------------------------------------------------------
+// Results to the caller: every field of the rows of several events widened to
+// the ABI's types and written straight into page-locked host memory in one
+// launch.  Bound by the host link (57 GB/s measured for one large copy): a
+// copy per event and field instead leaves it idle between copies (ten
+// 20,000-track events, 80 copies: 1.83 ms; this kernel: see launch_deliver).
+// A wavefront takes 64 rows: it reads them as one contiguous 8 KB run into
+// LDS (row stride 33 words: no bank conflicts either way) and writes each
+// field as one contiguous run, eight bytes a lane, so that the link carries
+// whole 64-byte pieces whatever the field.
+// `t`: kWave * kRecLds words of the wavefront's own; it takes every `step`-th
+// tile from `first` on.
+template <class Args>
+__device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first, int step, int lane)
+{
+    int j = 0;
+    for (int tile = uniform(first); tile < A.n_tiles; tile += step) {
+        while (j + 1 < A.n_jobs && A.job[j + 1].first_tile <= tile) ++j;
+        const auto &J = A.job[j];
+        const size_t r0 = (size_t)(tile - J.first_tile) * kDeliverTile;
+        const int m = min(kDeliverTile, J.n - (int)r0);
+        const float4 *src = reinterpret_cast<const float4 *>(J.rec + r0 * kRecWords);
+        float4 v[kRecWords / 4];
+#pragma unroll
+        for (int k = 0; k < kRecWords / 4; ++k) {
+            const int w = k * kWave + lane;
+            v[k] = (w >> 3) < m ? load_global(src + w) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int k = 0; k < kRecWords / 4; ++k) {
+            const int w = k * kWave + lane;
+            float *q = t + kRecLds * (w >> 3) + 4 * (w & 7);
+            q[0] = v[k].x; q[1] = v[k].y; q[2] = v[k].z; q[3] = v[k].w;
+        }
+        wave_lds_sync();
+        if (J.par) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const int w = k * kWave + lane, row = w / 6;
+                if (row < m) store_global(J.par + r0 * 6 + w, (double)t[kRecLds * row + w - 6 * row]);
+            }
+        }
+        if (J.cov) {
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                const int w = k * kWave + lane, row = w / 21;
+                if (row < m) store_global(J.cov + r0 * 21 + w, (double)t[kRecLds * row + kRecCov + w - 21 * row]);
+            }
+        }
+        if (lane < m) {
+            const float *row = t + kRecLds * lane;
+            const size_t r = r0 + lane;
+            const int nh = __float_as_int(row[kRecHits]), st = __float_as_int(row[kRecStatus]);
+            if (J.chi2) store_global(J.chi2 + r, (double)row[kRecChi2]);
+            if (J.n_hits) store_global(J.n_hits + r, nh);
+            if (J.n_holes) store_global(J.n_holes + r, __float_as_int(row[kRecHoles]));
+            // two measured coordinates per hit, minus the five track parameters
+            if (J.ndof) store_global(J.ndof + r, st < 0 ? 0 : 2 * nh - 5);
+            if (J.status) store_global(J.status + r, st);
+        }
+        if (J.hits_out) {
+            const int n = m * A.n_layers;
+            const int *src_h = J.hits + r0 * A.n_layers;
+            for (int w = lane; w < n; w += kWave) store_global(J.hits_out + r0 * A.n_layers + w, load_global(src_h + w));
+        }
+        wave_lds_sync();   // every row read before the next tile takes its place
+    }
+}
+
+constexpr int kDeliverLds = kWave * kRecLds * (int)sizeof(float);   // per wavefront
+
+template <int kJobs>
+__global__ void __launch_bounds__(256) k_deliver(const DeliverArgsT<kJobs> A)
+{
+    extern __shared__ int s_dyn[];
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    deliver_tiles(A, reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
+                  blockIdx.x * waves + wave, gridDim.x * waves, threadIdx.x & (kWave - 1));
+}
+
+// ---------------------------------------------------------------------------
 // Dynamic LDS of the batched builder: the per-layer records of every wave
 // (an int per lane and layer), then one SearchLds per wave.
 __host__ __device__ constexpr int search_lds_offset(int waves, int n_layers)
@@ -1330,8 +1415,16 @@ __host__ __device__ constexpr int search_lds_offset(int waves, int n_layers)
 // Batched builder.  Each wavefront takes work items (event, group of 64/G
 // seeds) - from a device counter when persistent, else from its block index -
 // and runs every building layer of its seeds with the state in registers.
+// With `D` (page-locked; as 2.6 KB of arguments it made every launch 1.9 us
+// later) one XCD's blocks, `deliver_blocks` of them, instead deliver the rows
+// that the launch before built, and the other XCDs share the building: the
+// host link works while the vector ALUs build, in one stream and with no
+// event between.  One XCD fills the link (20,000 rows beside 42,000 seeds 119
+// us, 102 the delivery alone), and its stores hold up only its own L2: spread
+// over all XCDs the delivering wavefronts stalled every build's loads behind
+// them (153 us, the sum of the two).
 template <int G, bool kStats, int kGeo>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_batch(const Params P, const BatchArgs B, int persistent)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_batch(const Params P, const BatchArgs B, int persistent, const DeliverArgs *__restrict__ D, int deliver_blocks)
 {
     extern __shared__ int s_dyn[];
     const int lane = threadIdx.x & (kWave - 1);
@@ -1339,7 +1432,24 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
     const int W = blockDim.x >> 6;
     Hist H{s_dyn + wave * P.n_layers * kWave, kWave};
     SearchLds<kGeo> &SL = reinterpret_cast<SearchLds<kGeo> *>(s_dyn + search_lds_offset(W, P.n_layers))[wave];
-    int item = (persistent ? (int)blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x)) * W + wave;
+    int item = B.first_item;
+    if (deliver_blocks > 0) {
+        // one XCD delivers, the others build
+        const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+        if (x == 0) {
+            typedef const __attribute__((address_space(4))) DeliverArgs CDeliver;
+            if (i < deliver_blocks)
+                deliver_tiles(*(CDeliver *)D, reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
+                              i * W + wave, deliver_blocks * W, lane);
+            return;
+        }
+        const int n = (B.end_item - B.first_item + W - 1) / W;   // building blocks
+        const int q = n / (kXcds - 1), r = n % (kXcds - 1), y = x - 1;
+        if (i >= q + (y < r ? 1 : 0)) return;
+        item += (y * q + min(y, r) + i) * W + wave;
+    } else {
+        item += xcd_contiguous(blockIdx.x, gridDim.x) * W + wave;
+    }
     for (;;) {
         if (persistent) {
             unsigned v = 0;
@@ -1347,7 +1457,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
             item = (int)__shfl(v, 0);
         }
         item = uniform(item);
-        if (item >= B.total_items) break;
+        if (item >= B.end_item) break;
         const int e = uniform(upper_bound_i32(B.item_prefix, B.n_events + 1, item) - 1);
         CEvent &E = event_desc(B.events, e);
         // the item's seeds, taken in azimuth order
@@ -1571,10 +1681,6 @@ __device__ __forceinline__ void fit_known(const Params &P, CEvent &E, const size
                     chi2, nupd, status);
     store_record(E.fit_rec + kRecWords * t, op, oc, chi2, nupd, P.n_layers - nupd, status, true);
 }
-
-// LDS stride of a result row staged for 64 rows' contiguous way out: odd, so
-// that the lanes' own rows fall on different banks.
-constexpr int kRecLds = kRecWords + 1;
 
 // The result rows of a wavefront's 64 consecutive tracks through LDS to
 // `out`, each store instruction one contiguous kilobyte.  `stage`: room for
@@ -1807,76 +1913,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
 }
 
 // ---------------------------------------------------------------------------
-// Results to the caller: every field of the rows of several events widened to
-// the ABI's types and written straight into page-locked host memory in one
-// launch.  Bound by the host link (57 GB/s measured for one large copy): a
-// copy per event and field instead leaves it idle between copies (ten
-// 20,000-track events, 80 copies: 1.83 ms; this kernel: see launch_deliver).
-// A wavefront takes 64 rows: it reads them as one contiguous 8 KB run into
-// LDS (row stride 33 words: no bank conflicts either way) and writes each
-// field as one contiguous run, eight bytes a lane, so that the link carries
-// whole 64-byte pieces whatever the field.
-__global__ void __launch_bounds__(256) k_deliver(const DeliverArgs A)
-{
-    extern __shared__ int s_dyn[];
-    const int lane = threadIdx.x & (kWave - 1);
-    float *t = reinterpret_cast<float *>(s_dyn) + (threadIdx.x >> 6) * (kWave * kRecLds);
-    const int step = gridDim.x * (blockDim.x >> 6);
-    int j = 0;
-    for (int tile = uniform(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); tile < A.n_tiles; tile += step) {
-        while (j + 1 < A.n_jobs && A.job[j + 1].first_tile <= tile) ++j;
-        const DeliverJob &J = A.job[j];
-        const size_t r0 = (size_t)(tile - J.first_tile) * kDeliverTile;
-        const int m = min(kDeliverTile, J.n - (int)r0);
-        const float4 *src = reinterpret_cast<const float4 *>(J.rec + r0 * kRecWords);
-        float4 v[kRecWords / 4];
-#pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k) {
-            const int w = k * kWave + lane;
-            v[k] = (w >> 3) < m ? load_global(src + w) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k) {
-            const int w = k * kWave + lane;
-            float *q = t + kRecLds * (w >> 3) + 4 * (w & 7);
-            q[0] = v[k].x; q[1] = v[k].y; q[2] = v[k].z; q[3] = v[k].w;
-        }
-        wave_lds_sync();
-        if (J.par) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                const int w = k * kWave + lane, row = w / 6;
-                if (row < m) store_global(J.par + r0 * 6 + w, (double)t[kRecLds * row + w - 6 * row]);
-            }
-        }
-        if (J.cov) {
-#pragma unroll
-            for (int k = 0; k < 21; ++k) {
-                const int w = k * kWave + lane, row = w / 21;
-                if (row < m) store_global(J.cov + r0 * 21 + w, (double)t[kRecLds * row + kRecCov + w - 21 * row]);
-            }
-        }
-        if (lane < m) {
-            const float *row = t + kRecLds * lane;
-            const size_t r = r0 + lane;
-            const int nh = __float_as_int(row[kRecHits]), st = __float_as_int(row[kRecStatus]);
-            if (J.chi2) store_global(J.chi2 + r, (double)row[kRecChi2]);
-            if (J.n_hits) store_global(J.n_hits + r, nh);
-            if (J.n_holes) store_global(J.n_holes + r, __float_as_int(row[kRecHoles]));
-            // two measured coordinates per hit, minus the five track parameters
-            if (J.ndof) store_global(J.ndof + r, st < 0 ? 0 : 2 * nh - 5);
-            if (J.status) store_global(J.status + r, st);
-        }
-        if (J.hits_out) {
-            const int n = m * A.n_layers;
-            const int *src_h = J.hits + r0 * A.n_layers;
-            for (int w = lane; w < n; w += kWave) store_global(J.hits_out + r0 * A.n_layers + w, load_global(src_h + w));
-        }
-        wave_lds_sync();   // every row read before the next tile takes its place
-    }
-}
-
-// ---------------------------------------------------------------------------
 // The no-allocation builder's batch descriptors: one fixed array in device
 // memory per GPU, kept until the process ends.  Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device.
@@ -1923,17 +1959,31 @@ hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s)
     return hipGetLastError();
 }
 
-// A wavefront per tile while few tiles leave the link idle; from 256 blocks
-// on, blocks take tiles in turn: 64 MB of stores run at 55.2 GB/s from 64
-// blocks of 256 threads, 54.3 from 256, and a delivery that overlaps a build
-// takes as few of its wavefront slots as that needs.
+// A wavefront per tile while few tiles leave the link idle; from 256 tiles
+// on, 256 wavefronts take tiles in turn: 64 MB of stores run at 55.2 GB/s from
+// 64 blocks of 256 threads, 54.3 from 256.  Few jobs travel in a short
+// argument list (2.6 KB of arguments make a launch 1.9 us later).
+constexpr int kDeliverWaves = 256;
+constexpr int kFewJobs = 2;
+
+template <int kJobs>
+static hipError_t launch_deliver_t(const DeliverArgsT<kJobs> &a, hipStream_t s)
+{
+    if (a.n_tiles <= kDeliverWaves) k_deliver<kJobs><<<a.n_tiles, kWave, kDeliverLds, s>>>(a);
+    else k_deliver<kJobs><<<kDeliverWaves / 4, 4 * kWave, 4 * kDeliverLds, s>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s)
 {
     if (a.n_tiles <= 0) return hipSuccess;
-    constexpr size_t lds = sizeof(float) * kWave * kRecLds;   // per wavefront
-    if (a.n_tiles <= 256) k_deliver<<<a.n_tiles, kWave, lds, s>>>(a);
-    else k_deliver<<<64, 256, 4 * lds, s>>>(a);
-    return hipGetLastError();
+    if (a.n_jobs > kFewJobs) return launch_deliver_t(a, s);
+    DeliverArgsT<kFewJobs> few;
+    few.n_jobs = a.n_jobs;
+    few.n_tiles = a.n_tiles;
+    few.n_layers = a.n_layers;
+    for (int j = 0; j < a.n_jobs; ++j) few.job[j] = a.job[j];
+    return launch_deliver_t(few, s);
 }
 
 hipError_t launch_calib_fma(float *dst, int n_blocks, int iters, hipStream_t s)
@@ -1994,29 +2044,36 @@ size_t build_lds_bytes(int geo, int n_layers, int wpb)
     return sizeof(int) * (size_t)search_lds_offset(wpb, n_layers) + (size_t)wpb * search;
 }
 
+// Wavefronts of a build launch that deliver: 16 / 64 / 256 of them took 126,
+// 119 and 123 us for 20,000 rows beside a build, 436, 421 and 417 for 82,000.
+constexpr int kOverlapWaves = 64;
+
 template <int G, bool kStats>
 static hipError_t launch_batch_t(const Params &p, const BatchArgs &b, int wpb, int persistent, int n_blocks,
-                                 hipStream_t s)
+                                 const DeliverArgs *d, hipStream_t s)
 {
-    const unsigned grid = persistent ? (unsigned)n_blocks : blocks_for(b.total_items, wpb);
+    const int dblocks = d && d->n_tiles > 0 ? std::max(1, kOverlapWaves / wpb) : 0;
+    unsigned grid = persistent ? (unsigned)n_blocks : blocks_for(b.end_item - b.first_item, wpb);
+    if (dblocks) grid = kXcds * std::max((unsigned)dblocks, (grid + kXcds - 2) / (kXcds - 1));
     if (grid == 0) return hipSuccess;
     const size_t hist = sizeof(int) * (size_t)search_lds_offset(wpb, p.n_layers);
+    auto lds = [&](size_t search) { return std::max(hist + wpb * search, (size_t)(d ? wpb * kDeliverLds : 0)); };
     switch (p.geo) {
-    case 0: k_build_batch<G, kStats, 0><<<grid, wpb * kWave, hist + wpb * sizeof(SearchLds<0>), s>>>(p, b, persistent); break;
-    case 1: k_build_batch<G, kStats, 1><<<grid, wpb * kWave, hist + wpb * sizeof(SearchLds<1>), s>>>(p, b, persistent); break;
-    case 2: k_build_batch<G, kStats, 2><<<grid, wpb * kWave, hist + wpb * sizeof(SearchLds<2>), s>>>(p, b, persistent); break;
-    case 3: k_build_batch<G, kStats, 3><<<grid, wpb * kWave, hist + wpb * sizeof(SearchLds<3>), s>>>(p, b, persistent); break;
+    case 0: k_build_batch<G, kStats, 0><<<grid, wpb * kWave, lds(sizeof(SearchLds<0>)), s>>>(p, b, persistent, d, dblocks); break;
+    case 1: k_build_batch<G, kStats, 1><<<grid, wpb * kWave, lds(sizeof(SearchLds<1>)), s>>>(p, b, persistent, d, dblocks); break;
+    case 2: k_build_batch<G, kStats, 2><<<grid, wpb * kWave, lds(sizeof(SearchLds<2>)), s>>>(p, b, persistent, d, dblocks); break;
+    case 3: k_build_batch<G, kStats, 3><<<grid, wpb * kWave, lds(sizeof(SearchLds<3>)), s>>>(p, b, persistent, d, dblocks); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int G, int wpb, int persistent, int n_blocks,
-                              bool stats, hipStream_t s)
+                              bool stats, const DeliverArgs *d, hipStream_t s)
 {
 #define MKF_BATCH_CASE(g)                                                                            \
-    case g: return stats ? launch_batch_t<g, true>(p, b, wpb, persistent, n_blocks, s)              \
-                         : launch_batch_t<g, false>(p, b, wpb, persistent, n_blocks, s);
+    case g: return stats ? launch_batch_t<g, true>(p, b, wpb, persistent, n_blocks, d, s)           \
+                         : launch_batch_t<g, false>(p, b, wpb, persistent, n_blocks, d, s);
     switch (G) {
         MKF_BATCH_CASE(1)
         MKF_BATCH_CASE(2)

@@ -700,7 +700,7 @@ static long long pack_states(const double *par, const double *cov, const int32_t
 // thickness or the 3x3 measurement), computed in FP64; seeds and tracks
 // FP32 states and covariances, finite, theta in (0, pi), hit indices in
 // range.  The layers and the seeds are packed in parallel for large events.
-// The seeds in order of the azimuth of their direction: a counting sort over
+// The seeds of each block of rows in order of the azimuth of their direction: a counting sort over
 // 1024 sectors that keeps the caller's order within a sector.  The batched
 // builder takes the seeds of one wavefront, and of the wavefronts that run
 // together, from neighbouring sectors, so the hits and bins their windows read
@@ -716,10 +716,14 @@ static inline uint16_t seed_sector(double phi)
 
 static void order_seeds(const std::vector<uint16_t> &sector, int *order)
 {
-    int start[kSeedSectors + 1] = {0};
-    for (uint16_t k : sector) ++start[k + 1];
-    for (int k = 0; k < kSeedSectors; ++k) start[k + 1] += start[k];
-    for (int i = 0; i < (int)sector.size(); ++i) order[start[sector[i]]++] = i;
+    for (int b0 = 0; b0 < (int)sector.size(); b0 += kSeedBlock) {
+        const int b1 = std::min((int)sector.size(), b0 + kSeedBlock);
+        int start[kSeedSectors + 1] = {0};
+        for (int i = b0; i < b1; ++i) ++start[sector[i] + 1];
+        start[0] = b0;
+        for (int k = 0; k < kSeedSectors; ++k) start[k + 1] += start[k];
+        for (int i = b0; i < b1; ++i) order[start[sector[i]]++] = i;
+    }
 }
 
 mkf_status pack_event(const mkf_event *ev, const EventShape &sh, int geo, void *image, int threads, std::string *why,
@@ -968,6 +972,8 @@ mkf_status compose_batch(EventRec *const *recs, int n, int spi, bool beam, char 
     args->total_tracks = (int)trks;
     args->total_seeds = (int)seeds;
     args->seeds_per_item = spi;
+    args->first_item = 0;
+    args->end_item = (int)items;
     args->all = all;
     args->layer_only = layer_only;
     args->max_chunks = max_chunks;
@@ -998,39 +1004,6 @@ mkf_status stage_batch(mkf_ctx *ctx, const std::vector<EventRec *> &recs, void *
             ctx->stage_pending = true;
         }
         if (own) ctx->staged_image.swap(image);
-    }
-    return MKF_OK;
-}
-
-// The batched pipeline on stream s: optional counter reset and re-index,
-// then the build kernel.
-mkf_status run_pipeline(mkf_ctx *ctx, const BatchArgs &args, const std::vector<EventRec *> &recs, uint32_t flags,
-                        bool timed, hipStream_t s)
-{
-    (void)recs;
-    return run_pipeline_with(ctx, ctx->params, ctx->tuning, args, flags, timed, s);
-}
-
-mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args,
-                             uint32_t flags, bool timed, hipStream_t s)
-{
-    const bool stats = flags & MKF_BATCH_STATS, reindex = flags & MKF_BATCH_REINDEX;
-    if (stats) MKF_HIP(launch_batch_zero(args, s));
-    if (reindex) {
-        if (timed) timer_begin(ctx, 1, s);
-        MKF_HIP(launch_index(P, args, s));
-    }
-    if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
-    if (timed && reindex) timer_switch(ctx, 1, 0, s, 1);   // one index build of the batch
-    else if (timed) timer_begin(ctx, 0, s);
-    MKF_HIP(launch_build_batch(P, args, t.lanes_per_seed, t.waves_per_block, t.persistent,
-                               ctx->n_cu * t.blocks_per_cu, stats, s));
-    if (flags & MKF_BATCH_FIT) {
-        if (timed) timer_switch(ctx, 0, 2, s, 1);
-        MKF_HIP(launch_refit(P, args, s));
-        if (timed) timer_end(ctx, 2, s, 1);
-    } else if (timed) {
-        timer_end(ctx, 0, s, 1);
     }
     return MKF_OK;
 }
@@ -1094,24 +1067,29 @@ static mkf_status ensure_pin(mkf_ctx *ctx, size_t bytes)
     return MKF_OK;
 }
 
-// Staging that lets `rows` result rows leave without another allocation.
-static size_t out_pin_bytes(size_t rows, int n_layers)
+// Padding of the staging of `sets` sets of rows in its slots.
+static size_t out_pad_bytes(size_t sets) { return 256 * kOutFields * (sets + kOutSlots); }
+
+// Staging that lets `rows` result rows of `sets` events leave without another
+// allocation.
+static size_t out_pin_bytes(size_t rows, size_t sets, int n_layers)
 {
     size_t row = 0;
     for (int f = 0; f < kOutFields; ++f) row += field_bytes(f, n_layers);
-    return std::min(kOutSlots * kOutSlotMax, row * rows + kOutSlots * 256 * kOutFields);
+    return std::min(kOutSlots * kOutSlotMax, row * rows + out_pad_bytes(sets));
 }
 
-namespace {
-
 // Result rows to the caller's arrays by launches of k_deliver on the
-// context's stream.  add() everything, then finish(), which waits for the
-// stream.  The staging is copied from by one thread: waking the packing
+// context's stream: add() everything, then finish(), which waits for the
+// stream.  A batched build calls place() for the rows of each of its parts as
+// it launches them and carries the pending ones in its next launch.  The
+// staging is copied from by one thread: waking the packing
 // threads for it took longer than they saved (event of 7,001 tracks 423 us
 // with 8 threads, 389 with one; fitted tracks of 8 x 5,000: 1,023 and 809).
 class Delivery {
   public:
-    explicit Delivery(mkf_ctx *ctx) : ctx_(ctx)
+    // fixed: no allocation, whatever staging the context has is used
+    explicit Delivery(mkf_ctx *ctx, bool fixed = false) : ctx_(ctx), fixed_(fixed)
     {
         args_.n_jobs = args_.n_tiles = 0;
         args_.n_layers = ctx->cfg.n_layers;
@@ -1125,7 +1103,9 @@ class Delivery {
     void add(const OutRows &o)
     {
         if (o.n <= 0) return;
-        Rows r{o, {}, 0};
+        const long long before = total_;
+        total_ += o.n;
+        Rows r{o, {}, 0, 0};
         bool any = false;
         const int nl = args_.n_layers;
         for (int f = 0; f < kOutFields; ++f) {
@@ -1136,26 +1116,45 @@ class Delivery {
             if (!r.direct[f]) r.staged += field_bytes(f, nl);
         }
         if (!any) return;
+        r.before = before;
         staged_ += r.staged * o.n;
+        for (int f = 0; f < kOutFields; ++f)
+            if (r.direct[f]) link_bytes_ += (double)field_bytes(f, nl) * o.n;
         rows_.push_back(r);
     }
 
-    mkf_status finish()
+    // Rows [first, end) of the rows added, in their order.
+    mkf_status place(long long first, long long end)
     {
         mkf_status st;
-        if (staged_) {
-            const size_t pad = 256 * kOutFields * (rows_.size() + kOutSlots);
-            const size_t want = (staged_ + pad + kOutSlots - 1) / kOutSlots;
-            slot_bytes_ = (std::min(std::max(want, kOutSlotMin), kOutSlotMax) + 255) & ~size_t(255);
-            if ((st = ensure_pin(ctx_, std::min(staged_ + pad, kOutSlots * slot_bytes_))) != MKF_OK) return st;
-            slot_bytes_ = std::min(slot_bytes_, ctx_->load_pin_bytes);
-            n_slots_ = (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
-            for (int k = 0; k < n_slots_; ++k)
-                if (!ctx_->out_done[k]) MKF_HIP(hipEventCreateWithFlags(&ctx_->out_done[k], hipEventDisableTiming));
+        if (!begun_ && (st = begin()) != MKF_OK) return st;
+        for (const Rows &r : rows_) {
+            const long long a = std::max(first - r.before, 0LL), b = std::min<long long>(end - r.before, r.o.n);
+            if (a < b && (st = place_rows(r, (int)a, (int)b)) != MKF_OK) return st;
         }
-        for (const Rows &r : rows_)
-            if ((st = place(r)) != MKF_OK) return st;
-        if ((st = launch()) != MKF_OK) return st;
+        placed_ = end;
+        return MKF_OK;
+    }
+
+    // The jobs placed and not launched, for a launch of the caller's that
+    // delivers them; launched() once it is queued.
+    const DeliverArgs &pending() const { return args_; }
+    mkf_status launched()
+    {
+        args_.n_jobs = args_.n_tiles = 0;
+        if (cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
+        return MKF_OK;
+    }
+
+    long long total_rows() const { return total_; }
+    // us per row on its way out: bytes over the host link, or copied out of
+    // the staging
+    double us_per_row() const { return total_ ? (link_bytes_ / 55e3 + staged_ / 28e3) / (double)total_ : 0.0; }
+
+    mkf_status finish()
+    {
+        mkf_status st = place(placed_, total_);
+        if (st != MKF_OK || (st = launch()) != MKF_OK) return st;
         for (int k = 1; k <= n_slots_; ++k)   // oldest first
             if ((st = empty(slot_[(cur_ + k) % n_slots_])) != MKF_OK) return st;
         MKF_HIP(hipStreamSynchronize(ctx_->stream));
@@ -1168,18 +1167,36 @@ class Delivery {
         OutRows o;
         void *direct[kOutFields];
         size_t staged;                  // bytes per row that go through the staging
+        long long before;               // rows added before these
     };
     struct Slot {
         std::vector<HostCopy> copies;   // not yet made
         hipEvent_t done = nullptr;
     };
 
+    mkf_status begin()
+    {
+        mkf_status st;
+        begun_ = true;
+        if (staged_) {
+            const size_t pad = out_pad_bytes(rows_.size());
+            const size_t want = (staged_ + pad + kOutSlots - 1) / kOutSlots;
+            slot_bytes_ = (std::min(std::max(want, kOutSlotMin), kOutSlotMax) + 255) & ~size_t(255);
+            const size_t least = 64 << 10;   // a tile of rows and more
+            const size_t want_pin = std::min(staged_ + pad, kOutSlots * slot_bytes_);
+            if ((!fixed_ || ctx_->load_pin_bytes < least) && (st = ensure_pin(ctx_, want_pin)) != MKF_OK) return st;
+            slot_bytes_ = std::min(slot_bytes_, ctx_->load_pin_bytes);
+            n_slots_ = (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
+        }
+        return MKF_OK;
+    }
+
     // jobs for the rows of r: all at once, or as many as a slot still holds
-    mkf_status place(const Rows &r)
+    mkf_status place_rows(const Rows &r, int r0, int r1)
     {
         const int nl = args_.n_layers;
-        for (int r0 = 0; r0 < r.o.n;) {
-            int m = r.o.n - r0;
+        while (r0 < r1) {
+            int m = r1 - r0;
             mkf_status st;
             if (r.staged) {
                 const size_t pad = 256 * kOutFields;
@@ -1217,9 +1234,7 @@ class Delivery {
     {
         if (args_.n_jobs == 0) return MKF_OK;
         MKF_HIP(launch_deliver(args_, ctx_->stream));
-        args_.n_jobs = args_.n_tiles = 0;
-        if (cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
-        return MKF_OK;
+        return launched();
     }
 
     mkf_status next_slot()
@@ -1243,13 +1258,136 @@ class Delivery {
     }
 
     mkf_ctx *ctx_;
+    const bool fixed_;
     DeliverArgs args_;
     std::vector<Rows> rows_;
     size_t staged_ = 0, slot_bytes_ = 0, used_ = 0;
+    double link_bytes_ = 0.0;
+    long long total_ = 0, placed_ = 0;
     Slot slot_[kOutSlots];
     int cur_ = -1, n_slots_ = 0;
-    bool finished_ = false;
+    bool begun_ = false, finished_ = false;
 };
+
+// How a batch whose rows go to the host is built: in parts (ends, in rows),
+// each part's rows delivered by the launch that builds the next, so that the
+// time is that of the longer of the two plus the first part's build and the
+// last one's delivery.  Parts end at blocks of kSeedBlock rows.  Chosen among
+// one part and sequences that start with a fraction of the rows and grow (for
+// rows that take longer to deliver than to build) or shrink, by the time that
+// a model of the launches gives, when it is at least 8 % shorter than that of
+// one part.  The model: a build takes `t0` (a wavefront's way through the
+// layers) plus `row` a seed, both in proportion to 0.45 + 0.55 of the fullest
+// layer's hits over 22,000, and 8/7 of it beside a delivery; a delivery takes
+// its bytes, a launch 4 us.  Measured with 6 candidates (us): thin cylinders
+// of 22,000 hits 10,240 seeds 50, 200,000 328, of 65,000 hits 10,240 seeds
+// 102, 50,000 213; disks of 11,000 hits 20,000 seeds 82, 40,000 104; deep
+// layers of 5,500 hits 20,000 seeds 86, of 22,000 hits 80,000 428.
+static std::vector<long long> plan_parts(const std::vector<EventLoad> &loads, const Params &P, double us_per_row)
+{
+    std::vector<long long> block;   // ends of the blocks
+    long long rows = 0;
+    double hits = 0.0;
+    for (const EventLoad &l : loads) {
+        for (int b = kSeedBlock; b < l.seeds; b += kSeedBlock) block.push_back(rows + b);
+        rows += l.seeds;
+        hits += (double)l.seeds * l.layer_hits;
+        if (l.seeds > 0) block.push_back(rows);
+    }
+    std::vector<long long> best{rows};
+    if (rows < 2 * kSeedBlock || us_per_row <= 0.0) return best;
+    const double dense = 0.45 + 0.55 * hits / (double)rows / 22000.0;
+    const double t0 = dense * (P.geo & 2 ? 58.0 : P.geo & 1 ? 55.0 : 33.0);
+    const double row = dense * (1.0 + P.max_cands) / 7.0 * (P.geo & 2 ? 4.6e-3 : P.geo & 1 ? 2.2e-3 : 1.48e-3);
+    auto time_of = [&](const std::vector<long long> &ends) {
+        double t = 0.0, out = 0.0;
+        long long at = 0;
+        for (long long e : ends) {
+            t += 4.0 + std::max((t0 + row * (double)(e - at)) * (at ? 8.0 / 7.0 : 1.0), out);
+            out = us_per_row * (double)(e - at);
+            at = e;
+        }
+        return t + 4.0 + out;
+    };
+    double best_t = 0.92 * time_of(best);
+    for (double first : {0.05, 0.1, 0.2, 0.33, 0.5, 0.62, 0.75})
+        for (double growth : {0.5, 1.0, 2.0, 3.0}) {
+            std::vector<long long> ends;
+            double want = first * (double)rows, size = want;
+            for (size_t k = 0; k < block.size() && (int)ends.size() + 1 < kBuildParts; ++k) {
+                if ((double)block[k] < want && k + 1 < block.size()) continue;
+                ends.push_back(block[k]);
+                size = std::max(size * growth, (double)kSeedBlock);
+                want = (double)block[k] + size;
+            }
+            if (ends.empty() || ends.back() < rows) ends.push_back(rows);
+            const double t = time_of(ends);
+            if (t < best_t) {
+                best_t = t;
+                best = ends;
+            }
+        }
+    return best;
+}
+
+// Work items of the first `rows` rows (whole blocks or events) of a batch.
+static int items_before(const std::vector<EventLoad> &loads, long long rows, int spi)
+{
+    long long items = 0;
+    for (const EventLoad &l : loads) {
+        const long long m = std::min<long long>(l.seeds, rows);
+        items += (m + spi - 1) / spi;
+        rows -= m;
+    }
+    return (int)items;
+}
+
+mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args, uint32_t flags,
+                        bool timed, hipStream_t s, Delivery *d, const std::vector<EventLoad> &loads)
+{
+    const bool stats = flags & MKF_BATCH_STATS, reindex = flags & MKF_BATCH_REINDEX;
+    if (stats) MKF_HIP(launch_batch_zero(args, s));
+    if (reindex) {
+        if (timed) timer_begin(ctx, 1, s);
+        MKF_HIP(launch_index(P, args, s));
+    }
+    if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
+    if (timed && reindex) timer_switch(ctx, 1, 0, s, 1);   // one index build of the batch
+    else if (timed) timer_begin(ctx, 0, s);
+    std::vector<long long> ends{0};   // one part, however many rows
+    if (d && !t.persistent) ends = plan_parts(loads, P, d->us_per_row());
+    if (ends.size() == 1) {
+        MKF_HIP(launch_build_batch(P, args, t.lanes_per_seed, t.waves_per_block, t.persistent,
+                                   ctx->n_cu * t.blocks_per_cu, stats, nullptr, s));
+    } else {
+        BatchArgs part = args;
+        long long at = 0;
+        for (size_t k = 0; k < ends.size(); ++k) {
+            part.first_item = k ? part.end_item : 0;
+            part.end_item = items_before(loads, ends[k], args.seeds_per_item);
+            DeliverArgs *jobs = nullptr;
+            mkf_status st;
+            if (k) {   // the rows of the part before
+                if ((st = d->place(at, ends[k - 1])) != MKF_OK) return st;
+                at = ends[k - 1];
+                jobs = ctx->build_jobs + k;
+                *jobs = d->pending();
+            }
+            MKF_HIP(launch_build_batch(P, part, t.lanes_per_seed, t.waves_per_block, 0, 0, stats, jobs, s));
+            if (k && (st = d->launched()) != MKF_OK) return st;
+        }
+    }
+    if (flags & MKF_BATCH_FIT) {
+        if (timed) timer_switch(ctx, 0, 2, s, 1);
+        MKF_HIP(launch_refit(P, args, s));
+        if (timed) timer_end(ctx, 2, s, 1);
+    } else if (timed) {
+        timer_end(ctx, 0, s, 1);
+    }
+    return MKF_OK;
+}
+
+namespace {
 
 OutRows build_rows(const EventRec *rec, const mkf_tracks &out)
 {
@@ -1264,12 +1402,11 @@ mkf_status deliver_one(mkf_ctx *ctx, const OutRows &o)
     return d.finish();
 }
 
-// The rows of a batch's events (outs may be null) and the wait for the stream.
-mkf_status deliver_batch(mkf_ctx *ctx, EventRec *const *recs, int n, const mkf_tracks *outs)
+std::vector<EventLoad> event_loads(EventRec *const *recs, int n)
 {
-    Delivery d(ctx);
-    for (int i = 0; outs && i < n; ++i) d.add(build_rows(recs[i], outs[i]));
-    return d.finish();
+    std::vector<EventLoad> c(n);
+    for (int i = 0; i < n; ++i) c[i] = EventLoad{recs[i]->shape.n_seeds, max_layer_hits(recs[i]->shape)};
+    return c;
 }
 
 }  // namespace
@@ -1333,8 +1470,11 @@ mkf_status mkf_create(const mkf_config *cfg, const mkf_allocator *alloc, void *h
     MKF_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
     if (khz <= 0) return fail(MKF_E_DEVICE, "device %d has no wall clock", dev);
     ctx->ms_per_tick = 1.0 / khz;
-    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), 3 * 2 * Timer::kRing * sizeof(unsigned long long),
+    constexpr size_t kStampBytes = 3 * 2 * Timer::kRing * sizeof(unsigned long long);
+    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), kStampBytes + kBuildParts * sizeof(DeliverArgs),
                           hipHostMallocDefault));
+    ctx->build_jobs = reinterpret_cast<DeliverArgs *>(reinterpret_cast<char *>(ctx->stamps) + kStampBytes);
+    for (hipEvent_t &ev : ctx->out_done) MKF_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     for (int k = 0; k < 3; ++k) {
         ctx->timers[k].start = ctx->stamps + (2 * k) * Timer::kRing;
         ctx->timers[k].stop = ctx->stamps + (2 * k + 1) * Timer::kRing;
@@ -1360,7 +1500,7 @@ void mkf_destroy(mkf_ctx *ctx)
     if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
     for (hipEvent_t e : ctx->out_done)
         if (e) (void)hipEventDestroy(e);
-    if (ctx->stamps) (void)hipHostFree(ctx->stamps);
+    if (ctx->stamps) (void)hipHostFree(ctx->stamps);   // and the build jobs behind them
     if (ctx->stage_done) (void)hipEventDestroy(ctx->stage_done);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1407,7 +1547,7 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
     // batch allocates none
     size_t rows = 0;
     for (const EventShape &sh : shapes) rows += (size_t)std::max(sh.n_seeds, sh.n_tracks);
-    mkf_status st = ensure_pin(ctx, std::max(off[n], out_pin_bytes(rows, ctx->cfg.n_layers)));
+    mkf_status st = ensure_pin(ctx, std::max(off[n], out_pin_bytes(rows, (size_t)n, ctx->cfg.n_layers)));
     if (st != MKF_OK) return st;
     char *pin = static_cast<char *>(ctx->load_pin);
     std::vector<std::unique_ptr<EventRec>> recs(n);
@@ -1576,7 +1716,9 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
         MKF_HIP(hipGraphLaunch(rec->plain_graph, ctx->stream));
         timer_end(ctx, 0, ctx->stream, n_launch);
     }
-    if ((st = deliver_batch(ctx, &rec, 1, out)) != MKF_OK) return st;
+    Delivery d(ctx);
+    if (out) d.add(build_rows(rec, *out));
+    if ((st = d.finish()) != MKF_OK) return st;
     timers_collect(ctx, true);
     return MKF_OK;
 }
@@ -1604,6 +1746,9 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
     bool need_index = false;
     if ((st = reindex_if_needed(ctx, recs, &need_index)) != MKF_OK) return st;
     if (need_index) flags |= MKF_BATCH_REINDEX;
+    std::unique_ptr<Delivery> d;   // none for an asynchronous batch: its destructor waits
+    if (!async) d = std::make_unique<Delivery>(ctx);
+    for (int i = 0; outs && i < n; ++i) d->add(build_rows(recs[i], outs[i]));
     const int spi = seeds_per_item(ctx->tuning.lanes_per_seed);
     if (flags & MKF_BATCH_GRAPH) {
         BatchGraph *bg = nullptr;
@@ -1634,7 +1779,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
             }
             hipGraph_t graph = nullptr;
             MKF_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
-            mkf_status cst = run_pipeline(ctx, args, recs, flags, false, ctx->stream);
+            mkf_status cst = run_pipeline(ctx, ctx->params, ctx->tuning, args, flags, false, ctx->stream);
             hipError_t end = hipStreamEndCapture(ctx->stream, &graph);
             if (cst != MKF_OK || end != hipSuccess) {
                 if (graph) (void)hipGraphDestroy(graph);
@@ -1658,13 +1803,15 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
         BatchArgs args{};
         if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, spi, &args, ctx->stream, beam)) != MKF_OK)
             return st;
-        if ((st = run_pipeline(ctx, args, recs, flags, true, ctx->stream)) != MKF_OK) return st;
+        if ((st = run_pipeline(ctx, ctx->params, ctx->tuning, args, flags, true, ctx->stream, d.get(),
+                               event_loads(recs.data(), n))) != MKF_OK)
+            return st;
     }
     if (async) {
         timers_collect(ctx, false);
         return MKF_OK;
     }
-    if ((st = deliver_batch(ctx, recs.data(), n, outs)) != MKF_OK) return st;
+    if ((st = d->finish()) != MKF_OK) return st;
     timers_collect(ctx, true);
     return MKF_OK;
 }
@@ -1713,13 +1860,17 @@ mkf_status mkf_build_batch_noalloc(mkf_ctx *ctx, const int32_t *handles, int32_t
         MKF_HIP(hipMemcpyAsync(dev, image, batch_scratch_bytes(n), hipMemcpyHostToDevice, ctx->stream));
         MKF_HIP(hipStreamSynchronize(ctx->stream));
     }
-    mkf_status st = run_pipeline_with(ctx, ctx->params, ctx->tuning, args, flags, true, ctx->stream);
+    std::unique_ptr<Delivery> d;
+    if (!async) d = std::make_unique<Delivery>(ctx, true);
+    for (int i = 0; outs && i < n; ++i) d->add(build_rows(recs[i], outs[i]));
+    mkf_status st = run_pipeline(ctx, ctx->params, ctx->tuning, args, flags, true, ctx->stream, d.get(),
+                                 event_loads(recs, n));
     if (st != MKF_OK) return st;
     if (async) {
         timers_collect(ctx, false);
         return MKF_OK;
     }
-    if ((st = deliver_batch(ctx, recs, n, outs)) != MKF_OK) return st;
+    if ((st = d->finish()) != MKF_OK) return st;
     timers_collect(ctx, true);
     return MKF_OK;
 }
@@ -1879,7 +2030,7 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     DevEvent hv{};
     const auto sizes = layout(nullptr, &hv);
     // the inputs now, the results later
-    if ((st = ensure_pin(ctx, std::max(sizes.first, out_pin_bytes(nt, (int)nl)))) != MKF_OK) return st;
+    if ((st = ensure_pin(ctx, std::max(sizes.first, out_pin_bytes(nt, 1, (int)nl)))) != MKF_OK) return st;
     layout(static_cast<char *>(ctx->load_pin), &hv);
     std::vector<int32_t> nh(nl);
     for (size_t L = 0; L < nl; ++L) nh[L] = rec->shape.layer_off[L + 1] - rec->shape.layer_off[L];

@@ -141,6 +141,7 @@ struct HostCopy {   // staged bytes to copy once the device has written them
 // a ring of slots, so that the device fills one while the host empties
 // another and large outputs need no staging of their size.
 constexpr int kOutSlots = 4;
+constexpr int kBuildParts = 8;   // parts a batch with host outputs is built in, at most
 constexpr size_t kOutSlotMin = size_t(512) << 10, kOutSlotMax = size_t(4) << 20;
 
 struct Server;   // serving state (mkf_serve.cpp)
@@ -182,6 +183,7 @@ struct mkf_ctx {
     // the stream, so it is free at the start of the next
     void *load_pin = nullptr;
     size_t load_pin_bytes = 0;
+    mkf::DeliverArgs *build_jobs = nullptr;         // page-locked: rows that build launches of the current call deliver
     hipEvent_t out_done[mkf::kOutSlots] = {};   // a slot of the result staging filled by the device
     std::vector<std::unique_ptr<mkf::BatchGraph>> graphs;
     mkf::Timer timers[3];
@@ -220,11 +222,16 @@ mkf_status ensure_beam(mkf_ctx *ctx, EventRec *rec);
 size_t batch_scratch_bytes(int n_events);
 int resolve_lanes(const mkf_ctx *ctx);
 int seeds_per_item(int G);
-mkf_status run_pipeline(mkf_ctx *ctx, const BatchArgs &args, const std::vector<EventRec *> &recs, uint32_t flags,
-                        bool timed, hipStream_t s);
-// the same with explicit parameters and launch shapes (serving keeps its own)
-mkf_status run_pipeline_with(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args,
-                             uint32_t flags, bool timed, hipStream_t s);
+// The batched pipeline on stream s: optional counter reset and re-index, then
+// the build and the final fit.  `d`: the way out of the results, which the
+// build launches then overlap, `loads` the events' sizes for it.  Serving keeps its own parameters and shapes.
+class Delivery;
+struct EventLoad {
+    int seeds;
+    int layer_hits;   // of its fullest layer
+};
+mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args, uint32_t flags,
+                        bool timed, hipStream_t s, Delivery *d = nullptr, const std::vector<EventLoad> &loads = {});
 // The fields of a result row (par, cov, chi2 in FP64, then hits, n_hits,
 // n_holes, ndof, status): bytes per row, array in mkf_tracks, array of a job.
 constexpr int kOutFields = 8;

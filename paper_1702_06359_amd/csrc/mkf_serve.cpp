@@ -187,7 +187,7 @@ struct Server {
         mkf_status st = stage_batch(ctx, recs, scratch_dev[si], scratch_host[si],
                                     seeds_per_item(tuning.lanes_per_seed), &args, s);
         if (st != MKF_OK) return st;
-        if ((st = run_pipeline_with(ctx, params, tuning, args, MKF_BATCH_REINDEX, false, s)) != MKF_OK) return st;
+        if ((st = run_pipeline(ctx, params, tuning, args, MKF_BATCH_REINDEX, false, s)) != MKF_OK) return st;
         DeliverArgs da;
         da.n_jobs = da.n_tiles = 0;
         da.n_layers = ctx->cfg.n_layers;

@@ -89,3 +89,30 @@ def test_fit_rows_at_every_layer_count(n_layers):
     # differences of positions of 50 cm against 0.01 cm errors: 50 / 0.01 * 6e-8 of a sigma per hit
     np.testing.assert_allclose(got["chi2"], ref["chi2"], rtol=3e-3, atol=3e-3)
     np.testing.assert_allclose(got["par"][:, :3], ref["par"][:, :3], rtol=0, atol=3e-4)
+
+
+# batches large enough to be built in parts, each delivered by the next part's launch: every lane count (seeds per
+# item), blocks of several wavefronts, four layers (a build's LDS below a delivery's), disks, deep layers, and events
+# that end within a block of 10,240 rows
+@pytest.mark.parametrize("cands,waves,layers,kind", [(6, 1, 10, "barrel"), (8, 2, 10, "barrel"), (1, 4, 4, "barrel"),
+                                                     (4, 1, 4, "barrel"), (2, 1, 10, "endcap"), (6, 1, 10, "thick")])
+def test_a_build_in_parts_is_the_build_in_one(cands, waves, layers, kind):
+    g = synth.Geometry.endcap(layers) if kind == "endcap" else synth.Geometry(
+        n_layers=layers, radii=tuple(4.0 * (i + 1) for i in range(layers)), x0=(0.002,) * layers,
+        thickness=(0.6,) * layers if kind == "thick" else None)
+    sizes = (20481, 1, 30007, 10240)
+    print("case parts", cands, waves, layers, kind, flush=True)
+    evs = [synth.make_event(n, cfg=33, event=i, noise=0.1, geometry=g) for i, n in enumerate(sizes)]
+    with abi.Context(abi.config_from_geometry(g, max_cands=cands)) as ctx:
+        ctx.set_tuning(waves_per_block=waves)
+        hs = ctx.load_events([abi.EventArrays.from_synth(e) for e in evs])
+        one = [abi.TrackArrays(n, layers) for n in sizes]
+        ctx.build_batch(hs, flags=abi.BATCH_ASYNC)   # one launch
+        for h, o in zip(hs, one):
+            abi.check(abi.lib().mkf_fetch_tracks(ctx.h, h, C.byref(o.tracks)))
+        for empty in (_pinned, None):
+            for _ in range(2):
+                parts = [abi.TrackArrays(n, layers, empty=empty) for n in sizes]
+                ctx.build_batch(hs, flags=abi.BATCH_REINDEX, outs=parts)
+                for a, b in zip(parts, one):
+                    _equal(a, b)
