@@ -1142,7 +1142,7 @@ class Delivery {
     mkf_status launched()
     {
         args_.n_jobs = args_.n_tiles = 0;
-        if (cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
+        if (n_slots_ > 1 && cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
         return MKF_OK;
     }
 
@@ -1155,9 +1155,11 @@ class Delivery {
     {
         mkf_status st = place(placed_, total_);
         if (st != MKF_OK || (st = launch()) != MKF_OK) return st;
-        for (int k = 1; k <= n_slots_; ++k)   // oldest first
-            if ((st = empty(slot_[(cur_ + k) % n_slots_])) != MKF_OK) return st;
+        if (n_slots_ > 1)
+            for (int k = 1; k <= n_slots_; ++k)   // oldest first
+                if ((st = empty(slot_[(cur_ + k) % n_slots_])) != MKF_OK) return st;
         MKF_HIP(hipStreamSynchronize(ctx_->stream));
+        if (n_slots_ == 1) copy_out(slot_[0]);
         finished_ = true;
         return MKF_OK;
     }
@@ -1182,11 +1184,12 @@ class Delivery {
             const size_t pad = out_pad_bytes(rows_.size());
             const size_t want = (staged_ + pad + kOutSlots - 1) / kOutSlots;
             slot_bytes_ = (std::min(std::max(want, kOutSlotMin), kOutSlotMax) + 255) & ~size_t(255);
+            if (staged_ + pad <= kOutOneSlot) slot_bytes_ = (staged_ + pad + 255) & ~size_t(255);
             const size_t least = 64 << 10;   // a tile of rows and more
             const size_t want_pin = std::min(staged_ + pad, kOutSlots * slot_bytes_);
             if ((!fixed_ || ctx_->load_pin_bytes < least) && (st = ensure_pin(ctx_, want_pin)) != MKF_OK) return st;
             slot_bytes_ = std::min(slot_bytes_, ctx_->load_pin_bytes);
-            n_slots_ = (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
+            n_slots_ = staged_ + pad <= slot_bytes_ ? 1 : (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
         }
         return MKF_OK;
     }
@@ -1251,10 +1254,16 @@ class Delivery {
     mkf_status empty(Slot &sl)
     {
         if (sl.copies.empty()) return MKF_OK;
-        MKF_HIP(hipEventSynchronize(sl.done));
+        if (n_slots_ > 1) MKF_HIP(hipEventSynchronize(sl.done));
+        else MKF_HIP(hipStreamSynchronize(ctx_->stream));
+        copy_out(sl);
+        return MKF_OK;
+    }
+
+    void copy_out(Slot &sl)
+    {
         for (const HostCopy &c : sl.copies) std::memcpy(c.dst, c.src, c.bytes);
         sl.copies.clear();
-        return MKF_OK;
     }
 
     mkf_ctx *ctx_;
