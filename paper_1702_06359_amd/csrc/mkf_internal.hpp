@@ -251,7 +251,8 @@ hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s);
 hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int lanes_per_seed, int waves_per_block,
                               int persistent, int n_blocks, bool stats, const DeliverArgs *deliver, hipStream_t s);
 hipError_t launch_build_layer(const Params &p, const DevEvent *ev_dev, const DevEvent &ev_host, int layer,
-                              int lanes_per_seed, int waves_per_block, bool stats, hipStream_t s);
+                              int lanes_per_seed, int seeds_per_wave, int waves_per_block, bool stats,
+                              hipStream_t s);
 hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s);
 hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s);
 hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s);

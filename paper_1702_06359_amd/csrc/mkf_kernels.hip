@@ -1462,7 +1462,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
         CEvent &E = event_desc(B.events, e);
         // the item's seeds, taken in azimuth order
         const int k = (item - B.item_prefix[e]) * B.seeds_per_item + lane / G;
-        const bool valid = lane < (kWave / G) * G && k < E.n_seeds;
+        const bool valid = lane < B.seeds_per_item * G && k < E.n_seeds;
         const int seed = valid ? load_global(E.seed_order + k) : E.n_seeds;
         Lane S;
         init_lane(S, E, P, valid ? seed : 0, valid && lane % G == 0);
@@ -1477,16 +1477,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
 // Per-layer builder: one event, one layer per launch, candidate state in
 // device memory (structure of arrays, slot = seed * G + rank) between layers.
 template <int G, bool kStats, int kGeo>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_layer(const Params P, const DevEvent *__restrict__ Ep, int L)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_layer(const Params P, const DevEvent *__restrict__ Ep, int L, int seeds_per_wave)
 {
     CEvent &E = event_desc(Ep, 0);
     const int lane = threadIdx.x & (kWave - 1);
     const int item = uniform(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    constexpr int kSeedsPerWave = kWave / G;
-    const int first = item * kSeedsPerWave;
+    const int first = item * seeds_per_wave;
     if (first >= E.n_seeds) return;
     const int seed = first + lane / G;
-    const bool valid = lane < kSeedsPerWave * G && seed < E.n_seeds;
+    const bool valid = lane < seeds_per_wave * G && seed < E.n_seeds;
     const int ns = E.st_slots;
     const int slot = item * kWave + lane;
     Hist H{E.st_hist + item * kWave, ns};
@@ -2086,29 +2085,29 @@ hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int G, int wp
 }
 
 template <int G, bool kStats>
-static hipError_t launch_layer_t(const Params &p, const DevEvent *ev_dev, int n_seeds, int L, int wpb,
-                                 hipStream_t s)
+static hipError_t launch_layer_t(const Params &p, const DevEvent *ev_dev, int n_seeds, int L, int spw,
+                                 int wpb, hipStream_t s)
 {
-    const int items = (n_seeds + kWave / G - 1) / (kWave / G);
+    const int items = (n_seeds + spw - 1) / spw;
     const unsigned grid = blocks_for(items, wpb);
     if (grid == 0) return hipSuccess;
     switch (p.geo) {
-    case 0: k_build_layer<G, kStats, 0><<<grid, wpb * kWave, wpb * sizeof(SearchLds<0>), s>>>(p, ev_dev, L); break;
-    case 1: k_build_layer<G, kStats, 1><<<grid, wpb * kWave, wpb * sizeof(SearchLds<1>), s>>>(p, ev_dev, L); break;
-    case 2: k_build_layer<G, kStats, 2><<<grid, wpb * kWave, wpb * sizeof(SearchLds<2>), s>>>(p, ev_dev, L); break;
-    case 3: k_build_layer<G, kStats, 3><<<grid, wpb * kWave, wpb * sizeof(SearchLds<3>), s>>>(p, ev_dev, L); break;
+    case 0: k_build_layer<G, kStats, 0><<<grid, wpb * kWave, wpb * sizeof(SearchLds<0>), s>>>(p, ev_dev, L, spw); break;
+    case 1: k_build_layer<G, kStats, 1><<<grid, wpb * kWave, wpb * sizeof(SearchLds<1>), s>>>(p, ev_dev, L, spw); break;
+    case 2: k_build_layer<G, kStats, 2><<<grid, wpb * kWave, wpb * sizeof(SearchLds<2>), s>>>(p, ev_dev, L, spw); break;
+    case 3: k_build_layer<G, kStats, 3><<<grid, wpb * kWave, wpb * sizeof(SearchLds<3>), s>>>(p, ev_dev, L, spw); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_build_layer(const Params &p, const DevEvent *ev_dev, const DevEvent &ev_host, int L, int G,
-                              int wpb, bool stats, hipStream_t s)
+                              int spw, int wpb, bool stats, hipStream_t s)
 {
     const int n = ev_host.n_seeds;
 #define MKF_LAYER_CASE(g)                                                                            \
-    case g: return stats ? launch_layer_t<g, true>(p, ev_dev, n, L, wpb, s)                          \
-                         : launch_layer_t<g, false>(p, ev_dev, n, L, wpb, s);
+    case g: return stats ? launch_layer_t<g, true>(p, ev_dev, n, L, spw, wpb, s)                          \
+                         : launch_layer_t<g, false>(p, ev_dev, n, L, spw, wpb, s);
     switch (G) {
         MKF_LAYER_CASE(1)
         MKF_LAYER_CASE(2)

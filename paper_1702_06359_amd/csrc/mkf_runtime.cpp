@@ -192,9 +192,8 @@ size_t carve_index(const EventShape &s, int nb, bool served, void *base, DevEven
     return c.off;
 }
 
-int plain_slots(int n_seeds, int G)
+int plain_slots(int n_seeds, int spw)
 {
-    const int spw = kWave / G;
     return ((n_seeds + spw - 1) / spw) * kWave;
 }
 
@@ -627,7 +626,21 @@ size_t batch_scratch_bytes(int n)
 }
 
 int resolve_lanes(const mkf_ctx *ctx) { return ctx->tuning.lanes_per_seed; }
-int seeds_per_item(int G) { return kWave / G; }
+int seeds_per_item(int geo, int G, long long seeds)
+{
+    const int most = kWave / G, resident = geo & 2 ? 1024 : 4096;
+    const long long want = std::max<long long>({(seeds + resident - 1) / resident, 5, (10 + G - 1) / G});
+    for (int spi : {5, 8, 10, 16, 20, 32, 40, 64})
+        if (spi >= want && spi < most) return spi;
+    return most;
+}
+
+int seeds_per_item(int geo, int G, EventRec *const *recs, int n)
+{
+    long long seeds = 0;
+    for (int i = 0; i < n; ++i) seeds += recs[i]->shape.n_seeds;
+    return seeds_per_item(geo, G, seeds);
+}
 
 // ---------------------------------------------------------------- events
 
@@ -1612,8 +1625,9 @@ mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_
     std::vector<EventRec *> raw(n);
     for (int i = 0; i < n; ++i) raw[i] = recs[i].get();
     BatchArgs args{};
-    if ((st = stage_batch(ctx, raw, ctx->batch_dev, ctx->batch_host, seeds_per_item(ctx->tuning.lanes_per_seed),
-                          &args, s)) != MKF_OK)
+    if ((st = stage_batch(ctx, raw, ctx->batch_dev, ctx->batch_host,
+                          seeds_per_item(ctx->params.geo, ctx->tuning.lanes_per_seed, raw.data(), n), &args, s)) !=
+        MKF_OK)
         return undo(st);
     hipError_t e = launch_index(ctx->params, args, s);
     if (e == hipSuccess) {
@@ -1677,10 +1691,11 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
     bool need_index = false;
     if ((st = reindex_if_needed(ctx, one, &need_index)) != MKF_OK) return st;
     const int G = ctx->tuning.lanes_per_seed, wpb = ctx->tuning.waves_per_block;
+    const int spi = seeds_per_item(ctx->params.geo, G, &rec, 1);
     if (need_index) {
         if ((st = ensure_batch_scratch(ctx, 1)) != MKF_OK) return st;
         BatchArgs args{};
-        if ((st = stage_batch(ctx, one, ctx->batch_dev, ctx->batch_host, seeds_per_item(G), &args, ctx->stream)) !=
+        if ((st = stage_batch(ctx, one, ctx->batch_dev, ctx->batch_host, spi, &args, ctx->stream)) !=
             MKF_OK)
             return st;
         MKF_HIP(launch_index(ctx->params, args, ctx->stream));
@@ -1689,7 +1704,7 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
         if (rec->plain) MKF_HIP(hipStreamSynchronize(ctx->stream));
         drop_plain_graph(rec);
         rec->heap->release(rec->plain);
-        const int slots = plain_slots(rec->shape.n_seeds, G);
+        const int slots = plain_slots(rec->shape.n_seeds, spi);
         const size_t bytes = carve_plain(rec->shape, slots, nullptr, &rec->view);
         rec->plain = rec->heap->alloc(bytes);
         if (!rec->plain) {
@@ -1708,7 +1723,7 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
             MKF_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
             hipError_t cap = hipSuccess;
             for (int L = rec->shape.n_seed_layers; L < rec->shape.n_layers && cap == hipSuccess; ++L)
-                cap = launch_build_layer(ctx->params, rec->dev_view, rec->view, L, G, wpb, false, ctx->stream);
+                cap = launch_build_layer(ctx->params, rec->dev_view, rec->view, L, G, spi, wpb, false, ctx->stream);
             hipError_t end = hipStreamEndCapture(ctx->stream, &graph);
             if (cap != hipSuccess || end != hipSuccess) {
                 if (graph) (void)hipGraphDestroy(graph);
@@ -1758,7 +1773,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
     std::unique_ptr<Delivery> d;   // none for an asynchronous batch: its destructor waits
     if (!async) d = std::make_unique<Delivery>(ctx);
     for (int i = 0; outs && i < n; ++i) d->add(build_rows(recs[i], outs[i]));
-    const int spi = seeds_per_item(ctx->tuning.lanes_per_seed);
+    const int spi = seeds_per_item(ctx->params.geo, ctx->tuning.lanes_per_seed, recs.data(), n);
     if (flags & MKF_BATCH_GRAPH) {
         BatchGraph *bg = nullptr;
         std::vector<int32_t> key(handles, handles + n);
@@ -1864,7 +1879,8 @@ mkf_status mkf_build_batch_noalloc(mkf_ctx *ctx, const int32_t *handles, int32_t
     BatchArgs args{};
     {
         std::lock_guard<std::mutex> lk(image_mu);
-        mkf_status st = compose_batch(recs, n, seeds_per_item(ctx->tuning.lanes_per_seed), false, image, dev, &args);
+        mkf_status st = compose_batch(recs, n, seeds_per_item(ctx->params.geo, ctx->tuning.lanes_per_seed, recs, n),
+                                      false, image, dev, &args);
         if (st != MKF_OK) return st;
         MKF_HIP(hipMemcpyAsync(dev, image, batch_scratch_bytes(n), hipMemcpyHostToDevice, ctx->stream));
         MKF_HIP(hipStreamSynchronize(ctx->stream));
@@ -1990,8 +2006,7 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     if (n == 0) return MKF_OK;
     if ((st = ensure_batch_scratch(ctx, n)) != MKF_OK) return st;
     BatchArgs args{};
-    if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, seeds_per_item(ctx->tuning.lanes_per_seed),
-                          &args, ctx->stream)) != MKF_OK)
+    if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, 64, &args, ctx->stream)) != MKF_OK)
         return st;
     timer_begin(ctx, 2, ctx->stream);
     MKF_HIP(launch_fit(ctx->params, args, ctx->stream));

@@ -225,7 +225,18 @@ mkf_status stage_batch(mkf_ctx *ctx, const std::vector<EventRec *> &recs, void *
 mkf_status ensure_beam(mkf_ctx *ctx, EventRec *rec);
 size_t batch_scratch_bytes(int n_events);
 int resolve_lanes(const mkf_ctx *ctx);
-int seeds_per_item(int G);
+// Seeds of a wavefront's work item, up to 64 / G lanes' worth: as many as keep
+// the batch's wavefronts resident at once (4,096; one a SIMD, 1,024, of the
+// deep-layer kernels, which gain nothing from more), for fewer search rounds
+// and smaller selections in each; at least five (fewer gain nothing) and ten
+// lanes; a divisor of kSeedBlock.
+// Measured (us; 6 candidates, ten / five seeds): 500 seeds 37.4 / 35.9, 5,000
+// 46.2 / 44.5, 20,000 68.4 / 62.4, on disks 123 / 94, but 40,000 82 / 116; one
+// candidate (64 / 16 / 10 / 5 seeds): 5,000 43 / 38 / 38 / 38, 20,000 59 / 43
+// / 42 / 48; deep layers 5,000 78 / 71, 20,000 (ten / eight)
+// 135 / 137.
+int seeds_per_item(int geo, int G, long long seeds);
+int seeds_per_item(int geo, int G, EventRec *const *recs, int n);
 // The batched pipeline on stream s: optional counter reset and re-index, then
 // the build and the final fit.  `d`: the way out of the results, which the
 // build launches then overlap, `loads` the events' sizes for it.  Serving keeps its own parameters and shapes.

@@ -185,7 +185,7 @@ struct Server {
         }
         BatchArgs args{};
         mkf_status st = stage_batch(ctx, recs, scratch_dev[si], scratch_host[si],
-                                    seeds_per_item(tuning.lanes_per_seed), &args, s);
+                                    seeds_per_item(params.geo, tuning.lanes_per_seed, recs.data(), (int)recs.size()), &args, s);
         if (st != MKF_OK) return st;
         if ((st = run_pipeline(ctx, params, tuning, args, MKF_BATCH_REINDEX, false, s)) != MKF_OK) return st;
         DeliverArgs da;
