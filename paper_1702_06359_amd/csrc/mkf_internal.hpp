@@ -244,6 +244,7 @@ void *noalloc_scratch(int device);              // its device address (null befo
 size_t build_lds_bytes(int geo, int n_layers, int waves_per_block);   // dynamic LDS of a batched build block
 hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s);
 hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s);   // b may be null
+hipError_t launch_mark(unsigned *flag, unsigned value, hipStream_t s);   // flag: page-locked
 hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s);   // work counters of a batch
 hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s);
 // deliver: page-locked, unchanged until the launch has run, or null: rows that

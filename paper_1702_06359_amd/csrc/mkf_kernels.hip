@@ -76,6 +76,15 @@ __global__ void k_stamp(unsigned long long *a, unsigned long long *b)
     if (b) __hip_atomic_store(b, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Tells the host that everything before it in the stream has been done and is
+// visible to it: the kernels before have finished and released their writes
+// to the device (stream order), the fence passes them on to the host.
+__global__ void k_mark(unsigned *flag, unsigned value)
+{
+    __threadfence_system();
+    __hip_atomic_store(flag, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Plain streaming copy used to calibrate memory-traffic counters.
 __global__ void k_copy16(const float4 *__restrict__ src, float4 *__restrict__ dst, size_t n)
 {
@@ -1946,6 +1955,12 @@ hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s)
 hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s)
 {
     k_stamp<<<1, 1, 0, s>>>(a, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_mark(unsigned *flag, unsigned value, hipStream_t s)
+{
+    k_mark<<<1, 1, 0, s>>>(flag, value);
     return hipGetLastError();
 }
 

@@ -1080,8 +1080,9 @@ static mkf_status ensure_pin(mkf_ctx *ctx, size_t bytes)
     return MKF_OK;
 }
 
-// Padding of the staging of `sets` sets of rows in its slots.
-static size_t out_pad_bytes(size_t sets) { return 256 * kOutFields * (sets + kOutSlots); }
+// Staging for `bytes` of `sets` sets of rows with the padding of their fields,
+// in however many slots.
+static size_t out_need_bytes(size_t bytes, size_t sets) { return bytes + 256 * kOutFields * (sets + 2 * kOutSlots); }
 
 // Staging that lets `rows` result rows of `sets` events leave without another
 // allocation.
@@ -1089,7 +1090,7 @@ static size_t out_pin_bytes(size_t rows, size_t sets, int n_layers)
 {
     size_t row = 0;
     for (int f = 0; f < kOutFields; ++f) row += field_bytes(f, n_layers);
-    return std::min(kOutSlots * kOutSlotMax, row * rows + out_pad_bytes(sets));
+    return std::min(kOutSlots * kOutSlotMax, out_need_bytes(row * rows, sets));
 }
 
 // Result rows to the caller's arrays by launches of k_deliver on the
@@ -1152,12 +1153,7 @@ class Delivery {
     // The jobs placed and not launched, for a launch of the caller's that
     // delivers them; launched() once it is queued.
     const DeliverArgs &pending() const { return args_; }
-    mkf_status launched()
-    {
-        args_.n_jobs = args_.n_tiles = 0;
-        if (n_slots_ > 1 && cur_ >= 0) MKF_HIP(hipEventRecord(ctx_->out_done[cur_], ctx_->stream));
-        return MKF_OK;
-    }
+    void launched() { args_.n_jobs = args_.n_tiles = 0; }
 
     long long total_rows() const { return total_; }
     // us per row on its way out: bytes over the host link, or copied out of
@@ -1168,11 +1164,17 @@ class Delivery {
     {
         mkf_status st = place(placed_, total_);
         if (st != MKF_OK || (st = launch()) != MKF_OK) return st;
-        if (n_slots_ > 1)
+        if (n_slots_ > 1) {
+            if ((st = mark_slot()) != MKF_OK) return st;
             for (int k = 1; k <= n_slots_; ++k)   // oldest first
                 if ((st = empty(slot_[(cur_ + k) % n_slots_])) != MKF_OK) return st;
-        MKF_HIP(hipStreamSynchronize(ctx_->stream));
-        if (n_slots_ == 1) copy_out(slot_[0]);
+            // the last mark was the last of the stream; but arrays written
+            // directly may be of a kind that only its end makes visible
+            if (link_bytes_ > 0.0) MKF_HIP(hipStreamSynchronize(ctx_->stream));
+        } else {
+            MKF_HIP(hipStreamSynchronize(ctx_->stream));
+            copy_out(slot_[0]);
+        }
         finished_ = true;
         return MKF_OK;
     }
@@ -1186,24 +1188,25 @@ class Delivery {
     };
     struct Slot {
         std::vector<HostCopy> copies;   // not yet made
-        hipEvent_t done = nullptr;
+        const unsigned *flag = nullptr; // `mark` once the device has filled the slot
+        unsigned mark = 0;
     };
 
     mkf_status begin()
     {
-        mkf_status st;
         begun_ = true;
-        if (staged_) {
-            const size_t pad = out_pad_bytes(rows_.size());
-            const size_t want = (staged_ + pad + kOutSlots - 1) / kOutSlots;
-            slot_bytes_ = (std::min(std::max(want, kOutSlotMin), kOutSlotMax) + 255) & ~size_t(255);
-            if (staged_ + pad <= kOutOneSlot) slot_bytes_ = (staged_ + pad + 255) & ~size_t(255);
-            const size_t least = 64 << 10;   // a tile of rows and more
-            const size_t want_pin = std::min(staged_ + pad, kOutSlots * slot_bytes_);
-            if ((!fixed_ || ctx_->load_pin_bytes < least) && (st = ensure_pin(ctx_, want_pin)) != MKF_OK) return st;
-            slot_bytes_ = std::min(slot_bytes_, ctx_->load_pin_bytes);
-            n_slots_ = staged_ + pad <= slot_bytes_ ? 1 : (int)std::min<size_t>(kOutSlots, ctx_->load_pin_bytes / slot_bytes_);
-        }
+        if (!staged_) return MKF_OK;
+        mkf_status st;
+        const size_t need = out_need_bytes(staged_, rows_.size());
+        const size_t least = 64 << 10;   // a tile of rows and more
+        if ((!fixed_ || ctx_->load_pin_bytes < least) &&
+            (st = ensure_pin(ctx_, std::min(need, kOutSlots * kOutSlotMax))) != MKF_OK)
+            return st;
+        // equal slots for everything where the staging holds it, else a ring
+        const size_t have = std::min(need, ctx_->load_pin_bytes);
+        n_slots_ = have < need ? kOutSlots : (int)std::min<size_t>(kOutSlots, std::max<size_t>(1, need / kOutSlotMin));
+        if (have / n_slots_ < least) n_slots_ = 1;
+        slot_bytes_ = have / n_slots_ & ~size_t(255);
         return MKF_OK;
     }
 
@@ -1250,25 +1253,46 @@ class Delivery {
     {
         if (args_.n_jobs == 0) return MKF_OK;
         MKF_HIP(launch_deliver(args_, ctx_->stream));
-        return launched();
+        launched();
+        return MKF_OK;
+    }
+
+    // everything placed in the current slot has been launched
+    mkf_status mark_slot()
+    {
+        Slot &sl = slot_[cur_];
+        if (sl.copies.empty()) return MKF_OK;
+        if (++ctx_->out_mark == 0) ++ctx_->out_mark;   // 0: never written
+        sl.mark = ctx_->out_mark;
+        sl.flag = ctx_->out_marks + cur_;
+        MKF_HIP(launch_mark(ctx_->out_marks + cur_, sl.mark, ctx_->stream));
+        return MKF_OK;
     }
 
     mkf_status next_slot()
     {
         mkf_status st = launch();   // ends the current slot's part
-        if (st != MKF_OK) return st;
+        if (st != MKF_OK || (cur_ >= 0 && (st = mark_slot()) != MKF_OK)) return st;
         cur_ = (cur_ + 1) % n_slots_;
         used_ = 0;
-        slot_[cur_].done = ctx_->out_done[cur_];
         return empty(slot_[cur_]);
     }
 
-    // waits until the device has filled the slot and copies its contents out
+    // Waits until the device has filled the slot and copies its contents out.
+    // The stream is asked from time to time, so that a failed launch ends the
+    // wait.
     mkf_status empty(Slot &sl)
     {
         if (sl.copies.empty()) return MKF_OK;
-        if (n_slots_ > 1) MKF_HIP(hipEventSynchronize(sl.done));
-        else MKF_HIP(hipStreamSynchronize(ctx_->stream));
+        for (unsigned spin = 1; __atomic_load_n(sl.flag, __ATOMIC_ACQUIRE) != sl.mark; ++spin) {
+            __builtin_ia32_pause();
+            if (spin % 8192) continue;   // some 100 us
+            const hipError_t e = hipStreamQuery(ctx_->stream);
+            if (e == hipErrorNotReady) continue;
+            MKF_HIP(e);
+            if (__atomic_load_n(sl.flag, __ATOMIC_ACQUIRE) != sl.mark)
+                return fail(MKF_E_DEVICE, "results: a finished launch left its mark unwritten");
+        }
         copy_out(sl);
         return MKF_OK;
     }
@@ -1396,7 +1420,7 @@ mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, cons
                 *jobs = d->pending();
             }
             MKF_HIP(launch_build_batch(P, part, t.lanes_per_seed, t.waves_per_block, 0, 0, stats, jobs, s));
-            if (k && (st = d->launched()) != MKF_OK) return st;
+            if (k) d->launched();
         }
     }
     if (flags & MKF_BATCH_FIT) {
@@ -1493,10 +1517,12 @@ mkf_status mkf_create(const mkf_config *cfg, const mkf_allocator *alloc, void *h
     if (khz <= 0) return fail(MKF_E_DEVICE, "device %d has no wall clock", dev);
     ctx->ms_per_tick = 1.0 / khz;
     constexpr size_t kStampBytes = 3 * 2 * Timer::kRing * sizeof(unsigned long long);
-    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), kStampBytes + kBuildParts * sizeof(DeliverArgs),
+    constexpr size_t kJobBytes = kBuildParts * sizeof(DeliverArgs), kMarkBytes = kOutSlots * sizeof(unsigned);
+    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), kStampBytes + kJobBytes + kMarkBytes,
                           hipHostMallocDefault));
     ctx->build_jobs = reinterpret_cast<DeliverArgs *>(reinterpret_cast<char *>(ctx->stamps) + kStampBytes);
-    for (hipEvent_t &ev : ctx->out_done) MKF_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    ctx->out_marks = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(ctx->build_jobs) + kJobBytes);
+    std::memset(ctx->out_marks, 0, kMarkBytes);
     for (int k = 0; k < 3; ++k) {
         ctx->timers[k].start = ctx->stamps + (2 * k) * Timer::kRing;
         ctx->timers[k].stop = ctx->stamps + (2 * k + 1) * Timer::kRing;
@@ -1520,9 +1546,7 @@ void mkf_destroy(mkf_ctx *ctx)
     ctx->heap.release(ctx->batch_dev);
     if (ctx->batch_host) (void)hipHostFree(ctx->batch_host);
     if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
-    for (hipEvent_t e : ctx->out_done)
-        if (e) (void)hipEventDestroy(e);
-    if (ctx->stamps) (void)hipHostFree(ctx->stamps);   // and the build jobs behind them
+    if (ctx->stamps) (void)hipHostFree(ctx->stamps);   // and the build jobs and marks behind them
     if (ctx->stage_done) (void)hipEventDestroy(ctx->stage_done);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1743,7 +1767,7 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
     Delivery d(ctx);
     if (out) d.add(build_rows(rec, *out));
     if ((st = d.finish()) != MKF_OK) return st;
-    timers_collect(ctx, true);
+    timers_collect(ctx, false);   // all has run
     return MKF_OK;
 }
 
@@ -1836,7 +1860,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
         return MKF_OK;
     }
     if ((st = d->finish()) != MKF_OK) return st;
-    timers_collect(ctx, true);
+    timers_collect(ctx, false);   // all has run
     return MKF_OK;
 }
 
@@ -1896,7 +1920,7 @@ mkf_status mkf_build_batch_noalloc(mkf_ctx *ctx, const int32_t *handles, int32_t
         return MKF_OK;
     }
     if ((st = d->finish()) != MKF_OK) return st;
-    timers_collect(ctx, true);
+    timers_collect(ctx, false);   // all has run
     return MKF_OK;
 }
 
@@ -2015,7 +2039,7 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     for (int i = 0; outs && i < n; ++i)
         d.add(OutRows{recs[i]->view.fit_rec, recs[i]->view.track_hits, recs[i]->shape.n_tracks, outs[i]});
     if ((st = d.finish()) != MKF_OK) return st;
-    timers_collect(ctx, true);
+    timers_collect(ctx, false);   // all has run
     return MKF_OK;
 }
 
@@ -2096,8 +2120,9 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
         if (out) d.add(OutRows{v.fit_rec, v.track_hits, n_tracks, *out});
         if ((st = d.finish()) != MKF_OK) return cleanup(st);
     }
-    timers_collect(ctx, true);
-    return cleanup(MKF_OK);
+    timers_collect(ctx, false);   // all has run
+    ctx->heap.release(buf);
+    return MKF_OK;
 }
 
 mkf_status mkf_timer_read(mkf_ctx *ctx, int32_t which, double *total_ms, int64_t *launches)

@@ -139,14 +139,15 @@ struct HostCopy {   // staged bytes to copy once the device has written them
 // (page-locked memory) are written directly, the others through page-locked
 // staging (the context's) that the host copies from.  The staging is used as
 // a ring of slots, so that the device fills one while the host empties
-// another and large outputs need no staging of their size; up to kOutOneSlot
-// bytes leave in one slot, copied after the stream's end, with no event (an
-// event recorded and waited for makes a call 20 us longer: 2,000 fitted tracks,
-// 576 KB, took 168 us in two slots).
+// another and large outputs need no staging of their size.  With several slots
+// the device tells the host of a filled one by a word that it waits for in a
+// loop (k_mark; an event recorded and waited for makes a call up to 20 us
+// longer: 20,000 tracks of one event built by mkf_build 393 us, 365 with
+// marks); up to twice kOutSlotMin leave in one slot, copied after the stream's
+// end (2,000 fitted tracks, 576 KB: 168 us in two slots, 121 in one).
 constexpr int kOutSlots = 4;
 constexpr int kBuildParts = 8;   // parts a batch with host outputs is built in, at most
 constexpr size_t kOutSlotMin = size_t(512) << 10, kOutSlotMax = size_t(4) << 20;
-constexpr size_t kOutOneSlot = size_t(1) << 20;
 
 struct Server;   // serving state (mkf_serve.cpp)
 struct ServerDeleter {
@@ -188,7 +189,8 @@ struct mkf_ctx {
     void *load_pin = nullptr;
     size_t load_pin_bytes = 0;
     mkf::DeliverArgs *build_jobs = nullptr;         // page-locked: rows that build launches of the current call deliver
-    hipEvent_t out_done[mkf::kOutSlots] = {};   // a slot of the result staging filled by the device
+    unsigned *out_marks = nullptr;                  // page-locked: one a slot of the result staging (k_mark)
+    unsigned out_mark = 0;                          // the last value used
     std::vector<std::unique_ptr<mkf::BatchGraph>> graphs;
     mkf::Timer timers[3];
     unsigned long long *stamps = nullptr;       // their rings, page-locked
