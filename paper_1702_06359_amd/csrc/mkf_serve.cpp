@@ -27,25 +27,38 @@ constexpr int kStreams = 4;
 
 size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Reuses pinned host buffers by power-of-two size class.  A buffer is kept for
-// the use it had (inputs or results): an input buffer stays in the cache of the
-// threads that pack into it instead of coming back from the one that copies
-// results out (one submit of 10,900 seeds: 151 against 319 us).  Where its own
-// use has none free it takes one of the other's before making a new one.
+// Page-locked staging, inputs and results apart: an input buffer so stays in
+// the cache of the threads that pack into it instead of coming back from the
+// one that copies results out (one submit of 10,900 seeds: 151 against 319 us).
+// Taken from two slabs made at configuration (page-locking a buffer as it is
+// first needed took most of a submit: 16 submits 7.5-10 ms); when a slab is
+// full, from buffers reused by power-of-two size class.
 class PinnedPool {
   public:
     enum Use { kInput, kResult };
 
+    // slabs of `bytes` each; without them where they cannot be had
+    void reserve(size_t bytes)
+    {
+        if (hipHostMalloc(reinterpret_cast<void **>(&base_), 2 * bytes, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            base_ = nullptr;
+            return;
+        }
+        for (int u = 0; u < 2; ++u) slab_[u] = std::make_unique<SlabHeap>(base_ + u * bytes, bytes);
+    }
     void *get(size_t bytes, Use use, size_t *cls)
     {
+        *cls = 0;   // from the slab
+        if (slab_[use])
+            if (void *p = slab_[use]->alloc(bytes)) return p;
         size_t c = 4096;
         while (c < bytes) c <<= 1;
         *cls = c;
         {
             std::lock_guard<std::mutex> lk(mu_);
-            for (int u : {(int)use, 1 - (int)use}) {
-                auto it = free_[u].find(c);
-                if (it == free_[u].end() || it->second.empty()) continue;
+            auto it = free_[use].find(c);
+            if (it != free_[use].end() && !it->second.empty()) {
                 void *p = it->second.back();
                 it->second.pop_back();
                 return p;
@@ -58,6 +71,10 @@ class PinnedPool {
     void put(void *p, Use use, size_t cls)
     {
         if (!p) return;
+        if (cls == 0) {
+            slab_[use]->release(p);
+            return;
+        }
         std::lock_guard<std::mutex> lk(mu_);
         free_[use][cls].push_back(p);
     }
@@ -66,10 +83,13 @@ class PinnedPool {
         for (auto &m : free_)
             for (auto &kv : m)
                 for (void *p : kv.second) (void)hipHostFree(p);
+        if (base_) (void)hipHostFree(base_);
     }
 
   private:
     std::mutex mu_;
+    char *base_ = nullptr;
+    std::unique_ptr<SlabHeap> slab_[2];
     std::map<size_t, std::vector<void *>> free_[2];
 };
 
@@ -365,6 +385,8 @@ mkf_status mkf_serve_config(mkf_ctx *ctx, uint64_t hbm_budget_bytes, int32_t max
             return undo(fail(MKF_E_NOMEM, "pinned batch descriptors: %s", hipGetErrorString(e)));
         }
     }
+    // as much of each as the budget could hold in flight, up to 32 MiB
+    sv->pinned.reserve(std::min<size_t>(hbm_budget_bytes / 2 & ~uint64_t(4095), size_t(32) << 20));
     ctx->server = std::move(sv);
     Server *raw = ctx->server.get();
     raw->thr = std::thread([raw] { raw->loop(); });
