@@ -240,23 +240,29 @@ constexpr size_t kNoAllocScratchBytes =
 hipError_t noalloc_scratch_init(int device);   // with `device` current; once per device
 void *noalloc_scratch(int device);              // its device address (null before init)
 
+// Where a launch puts the time at its start (page-locked words; null: nowhere).
+struct Stamp {
+    unsigned long long *a = nullptr, *b = nullptr;
+};
+
 // Launch helpers implemented in mkf_kernels.hip.
 size_t build_lds_bytes(int geo, int n_layers, int waves_per_block);   // dynamic LDS of a batched build block
 hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s);
-hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s);   // b may be null
+hipError_t launch_stamp(const Stamp &st, hipStream_t s);
 hipError_t launch_mark(unsigned *flag, unsigned value, hipStream_t s);   // flag: page-locked
 hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s);   // work counters of a batch
-hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s);
+hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st = {});
 // deliver: page-locked, unchanged until the launch has run, or null: rows that
 // the launch delivers beside its build (not a persistent one)
 hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int lanes_per_seed, int waves_per_block,
-                              int persistent, int n_blocks, bool stats, const DeliverArgs *deliver, hipStream_t s);
+                              int persistent, int n_blocks, bool stats, const DeliverArgs *deliver, hipStream_t s,
+                              const Stamp &st = {});
 hipError_t launch_build_layer(const Params &p, const DevEvent *ev_dev, const DevEvent &ev_host, int layer,
                               int lanes_per_seed, int seeds_per_wave, int waves_per_block, bool stats,
                               hipStream_t s);
-hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s);
-hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s);
-hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s);
+hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st = {});
+hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st = {});
+hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s, const Stamp &st = {});
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 hipError_t launch_calib_fma(float *dst, int n_blocks, int iters, hipStream_t s);   // iters: multiple of 4
 int calib_fma_chains();

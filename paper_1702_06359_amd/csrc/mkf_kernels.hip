@@ -76,6 +76,17 @@ __global__ void k_stamp(unsigned long long *a, unsigned long long *b)
     if (b) __hip_atomic_store(b, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The same at the start of another kernel, from its first block: a phase that
+// begins with a launch, or ends where the next launch begins, needs none of
+// its own.
+__device__ __forceinline__ void stamp_start(const Stamp &st)
+{
+    if (st.a == nullptr || (blockIdx.x | blockIdx.y | threadIdx.x) != 0) return;
+    const unsigned long long t = (unsigned long long)wall_clock64();
+    __hip_atomic_store(st.a, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (st.b) __hip_atomic_store(st.b, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Tells the host that everything before it in the stream has been done and is
 // visible to it: the kernels before have finished and released their writes
 // to the device (stream order), the fence passes them on to the host.
@@ -291,10 +302,12 @@ __device__ __forceinline__ void lds_scan_counts(unsigned *s_cnt, int nr, int car
 template <bool kShort>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) k_index_layer(const Params P,
                                                                                                    const BatchArgs B,
-                                                                                                   int only)
+                                                                                                   int only,
+                                                                                                   const Stamp st)
 {
     extern __shared__ unsigned s_cnt[];
     __shared__ int s_wave[16];
+    stamp_start(st);
     const int e = blockIdx.x / P.n_layers;
     const int L = blockIdx.x - e * P.n_layers;
     CEvent &E = event_desc(B.events, e);
@@ -377,9 +390,10 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
 // 2 x 64 hits each thread went through whatever the split), no counter leaves
 // LDS, and the last pass writes into one run of lines per block, which so
 // leave its L2 whole.
-__global__ void __launch_bounds__(kBlockThreads) k_index_hist(const Params P, const BatchArgs B)
+__global__ void __launch_bounds__(kBlockThreads) k_index_hist(const Params P, const BatchArgs B, const Stamp st)
 {
     __shared__ int s_n[kBuckets];
+    stamp_start(st);
     const int e = blockIdx.y / P.n_layers;
     const int L = blockIdx.y - e * P.n_layers;
     CEvent &E = event_desc(B.events, e);
@@ -1405,9 +1419,10 @@ __device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first
 constexpr int kDeliverLds = kWave * kRecLds * (int)sizeof(float);   // per wavefront
 
 template <int kJobs>
-__global__ void __launch_bounds__(256) k_deliver(const DeliverArgsT<kJobs> A)
+__global__ void __launch_bounds__(256) k_deliver(const DeliverArgsT<kJobs> A, const Stamp st)
 {
     extern __shared__ int s_dyn[];
+    stamp_start(st);
     const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     deliver_tiles(A, reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
                   blockIdx.x * waves + wave, gridDim.x * waves, threadIdx.x & (kWave - 1));
@@ -1433,9 +1448,10 @@ __host__ __device__ constexpr int search_lds_offset(int waves, int n_layers)
 // over all XCDs the delivering wavefronts stalled every build's loads behind
 // them (153 us, the sum of the two).
 template <int G, bool kStats, int kGeo>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_batch(const Params P, const BatchArgs B, int persistent, const DeliverArgs *__restrict__ D, int deliver_blocks)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_build_batch(const Params P, const BatchArgs B, int persistent, const DeliverArgs *__restrict__ D, int deliver_blocks, const Stamp st)
 {
     extern __shared__ int s_dyn[];
+    stamp_start(st);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const int W = blockDim.x >> 6;
@@ -1729,9 +1745,10 @@ __host__ __device__ constexpr int fit_lds_words(int n_layers)
 // its neighbour's); a wavefront across a batch boundary, or at the end of
 // the grid, takes one pass per batch with per-lane accesses instead.
 template <int kGeo>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_fit(const Params P, const BatchArgs B)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_fit(const Params P, const BatchArgs B, const Stamp st)
 {
     extern __shared__ int s_dyn[];
+    stamp_start(st);
     const int lane = threadIdx.x & (kWave - 1);
     const int g0 = uniform(xcd_contiguous(blockIdx.x, gridDim.x) * blockDim.x + (threadIdx.x & ~(kWave - 1)));
     if (g0 >= B.total_tracks) return;
@@ -1871,9 +1888,10 @@ __device__ __forceinline__ void refit_built(const Params &P, CEvent &E, const si
 // and their results out through LDS (as the fit does), so that each transfer
 // is one contiguous run instead of 64 rows 40 to 168 bytes apart.
 template <int kGeo>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_refit(const Params P, const BatchArgs B)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xyz(kGeo) ? 3 : 4))) k_refit(const Params P, const BatchArgs B, const Stamp st)
 {
     extern __shared__ int s_dyn[];
+    stamp_start(st);
     const int lane = threadIdx.x & (kWave - 1);
     const int g0 = uniform(xcd_contiguous(blockIdx.x, gridDim.x) * blockDim.x + (threadIdx.x & ~(kWave - 1)));
     if (g0 >= B.total_seeds) return;
@@ -1952,9 +1970,10 @@ hipError_t launch_fill_i32(int *ptr, int value, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_stamp(unsigned long long *a, unsigned long long *b, hipStream_t s)
+hipError_t launch_stamp(const Stamp &st, hipStream_t s)
 {
-    k_stamp<<<1, 1, 0, s>>>(a, b);
+    if (!st.a) return hipSuccess;
+    k_stamp<<<1, 1, 0, s>>>(st.a, st.b);
     return hipGetLastError();
 }
 
@@ -1981,23 +2000,23 @@ constexpr int kDeliverWaves = 256;
 constexpr int kFewJobs = 2;
 
 template <int kJobs>
-static hipError_t launch_deliver_t(const DeliverArgsT<kJobs> &a, hipStream_t s)
+static hipError_t launch_deliver_t(const DeliverArgsT<kJobs> &a, const Stamp &st, hipStream_t s)
 {
-    if (a.n_tiles <= kDeliverWaves) k_deliver<kJobs><<<a.n_tiles, kWave, kDeliverLds, s>>>(a);
-    else k_deliver<kJobs><<<kDeliverWaves / 4, 4 * kWave, 4 * kDeliverLds, s>>>(a);
+    if (a.n_tiles <= kDeliverWaves) k_deliver<kJobs><<<a.n_tiles, kWave, kDeliverLds, s>>>(a, st);
+    else k_deliver<kJobs><<<kDeliverWaves / 4, 4 * kWave, 4 * kDeliverLds, s>>>(a, st);
     return hipGetLastError();
 }
 
-hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s)
+hipError_t launch_deliver(const DeliverArgs &a, hipStream_t s, const Stamp &st)
 {
-    if (a.n_tiles <= 0) return hipSuccess;
-    if (a.n_jobs > kFewJobs) return launch_deliver_t(a, s);
+    if (a.n_tiles <= 0) return launch_stamp(st, s);
+    if (a.n_jobs > kFewJobs) return launch_deliver_t(a, st, s);
     DeliverArgsT<kFewJobs> few;
     few.n_jobs = a.n_jobs;
     few.n_tiles = a.n_tiles;
     few.n_layers = a.n_layers;
     for (int j = 0; j < a.n_jobs; ++j) few.job[j] = a.job[j];
-    return launch_deliver_t(few, s);
+    return launch_deliver_t(few, st, s);
 }
 
 hipError_t launch_calib_fma(float *dst, int n_blocks, int iters, hipStream_t s)
@@ -2015,18 +2034,19 @@ hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s)
     return hipGetLastError();
 }
 
-static hipError_t launch_index_layer(const Params &p, const BatchArgs &b, const IndexExtent &x, int only, hipStream_t s)
+static hipError_t launch_index_layer(const Params &p, const BatchArgs &b, const IndexExtent &x, int only,
+                                     const Stamp &st, hipStream_t s)
 {
     const unsigned blocks = (unsigned)(b.n_events * p.n_layers);
     const size_t lds = layer_block_lds(x.layer_hits, x.bins);
-    if (x.layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, lds, s>>>(p, b, only);
-    else k_index_layer<false><<<blocks, 1024, lds, s>>>(p, b, only);
+    if (x.layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, lds, s>>>(p, b, only, st);
+    else k_index_layer<false><<<blocks, 1024, lds, s>>>(p, b, only, st);
     return hipGetLastError();
 }
 
-hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s)
+hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st)
 {
-    if (b.total_hits <= 0) return hipSuccess;
+    if (b.total_hits <= 0) return launch_stamp(st, s);
     const unsigned pairs = (unsigned)(b.n_events * p.n_layers);
     // One block per (event, layer) or the bucketed build, whichever is sooner
     // done.  Measured (us): a block takes 7 + 2.05 per 1,000 hits of the
@@ -2038,9 +2058,9 @@ hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s)
     const double by_layer = 7.0 + 2.05e-3 * b.all.layer_hits;
     const double bucketed = 14.0 + 1.65e-5 * b.total_hits + 0.083 * pairs;
     if (b.layer_only.events == b.n_events || (by_layer < bucketed && layer_block_fits(b.all.layer_hits, b.all.bins)))
-        return launch_index_layer(p, b, b.all, 0, s);
+        return launch_index_layer(p, b, b.all, 0, st, s);
     const dim3 grid((unsigned)std::max(1, b.max_chunks), pairs);
-    k_index_hist<<<grid, kBlockThreads, 0, s>>>(p, b);
+    k_index_hist<<<grid, kBlockThreads, 0, s>>>(p, b, st);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     k_index_part<<<grid, kBlockThreads, 0, s>>>(p, b);
@@ -2049,7 +2069,7 @@ hipError_t launch_index(const Params &p, const BatchArgs &b, hipStream_t s)
     k_index_place<<<dim3(kBuckets, pairs), kBlockThreads, sizeof(unsigned) << b.max_bucket_shift, s>>>(p, b);
     err = hipGetLastError();
     if (err != hipSuccess || b.layer_only.events == 0) return err;
-    return launch_index_layer(p, b, b.layer_only, 1, s);
+    return launch_index_layer(p, b, b.layer_only, 1, Stamp{}, s);
 }
 
 size_t build_lds_bytes(int geo, int n_layers, int wpb)
@@ -2064,30 +2084,30 @@ constexpr int kOverlapWaves = 64;
 
 template <int G, bool kStats>
 static hipError_t launch_batch_t(const Params &p, const BatchArgs &b, int wpb, int persistent, int n_blocks,
-                                 const DeliverArgs *d, hipStream_t s)
+                                 const DeliverArgs *d, hipStream_t s, const Stamp &st)
 {
     const int dblocks = d && d->n_tiles > 0 ? std::max(1, kOverlapWaves / wpb) : 0;
     unsigned grid = persistent ? (unsigned)n_blocks : blocks_for(b.end_item - b.first_item, wpb);
     if (dblocks) grid = kXcds * std::max((unsigned)dblocks, (grid + kXcds - 2) / (kXcds - 1));
-    if (grid == 0) return hipSuccess;
+    if (grid == 0) return launch_stamp(st, s);
     const size_t hist = sizeof(int) * (size_t)search_lds_offset(wpb, p.n_layers);
     auto lds = [&](size_t search) { return std::max(hist + wpb * search, (size_t)(d ? wpb * kDeliverLds : 0)); };
     switch (p.geo) {
-    case 0: k_build_batch<G, kStats, 0><<<grid, wpb * kWave, lds(sizeof(SearchLds<0>)), s>>>(p, b, persistent, d, dblocks); break;
-    case 1: k_build_batch<G, kStats, 1><<<grid, wpb * kWave, lds(sizeof(SearchLds<1>)), s>>>(p, b, persistent, d, dblocks); break;
-    case 2: k_build_batch<G, kStats, 2><<<grid, wpb * kWave, lds(sizeof(SearchLds<2>)), s>>>(p, b, persistent, d, dblocks); break;
-    case 3: k_build_batch<G, kStats, 3><<<grid, wpb * kWave, lds(sizeof(SearchLds<3>)), s>>>(p, b, persistent, d, dblocks); break;
+    case 0: k_build_batch<G, kStats, 0><<<grid, wpb * kWave, lds(sizeof(SearchLds<0>)), s>>>(p, b, persistent, d, dblocks, st); break;
+    case 1: k_build_batch<G, kStats, 1><<<grid, wpb * kWave, lds(sizeof(SearchLds<1>)), s>>>(p, b, persistent, d, dblocks, st); break;
+    case 2: k_build_batch<G, kStats, 2><<<grid, wpb * kWave, lds(sizeof(SearchLds<2>)), s>>>(p, b, persistent, d, dblocks, st); break;
+    case 3: k_build_batch<G, kStats, 3><<<grid, wpb * kWave, lds(sizeof(SearchLds<3>)), s>>>(p, b, persistent, d, dblocks, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_build_batch(const Params &p, const BatchArgs &b, int G, int wpb, int persistent, int n_blocks,
-                              bool stats, const DeliverArgs *d, hipStream_t s)
+                              bool stats, const DeliverArgs *d, hipStream_t s, const Stamp &st)
 {
 #define MKF_BATCH_CASE(g)                                                                            \
-    case g: return stats ? launch_batch_t<g, true>(p, b, wpb, persistent, n_blocks, d, s)           \
-                         : launch_batch_t<g, false>(p, b, wpb, persistent, n_blocks, d, s);
+    case g: return stats ? launch_batch_t<g, true>(p, b, wpb, persistent, n_blocks, d, s, st)           \
+                         : launch_batch_t<g, false>(p, b, wpb, persistent, n_blocks, d, s, st);
     switch (G) {
         MKF_BATCH_CASE(1)
         MKF_BATCH_CASE(2)
@@ -2134,35 +2154,35 @@ hipError_t launch_build_layer(const Params &p, const DevEvent *ev_dev, const Dev
 #undef MKF_LAYER_CASE
 }
 
-hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s)
+hipError_t launch_refit(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st)
 {
-    if (b.total_seeds <= 0) return hipSuccess;
+    if (b.total_seeds <= 0) return launch_stamp(st, s);
     const unsigned grid = blocks_for(b.total_seeds, 256);
     const size_t lds = 4 * sizeof(int) * (size_t)fit_lds_words(p.n_layers);
     switch (p.geo | (p.update3d ? 4 : 0)) {
-    case 0: k_refit<0><<<grid, 256, lds, s>>>(p, b); break;
-    case 1: k_refit<1><<<grid, 256, lds, s>>>(p, b); break;
-    case 2: k_refit<2><<<grid, 256, lds, s>>>(p, b); break;
-    case 3: k_refit<3><<<grid, 256, lds, s>>>(p, b); break;
-    case 6: k_refit<6><<<grid, 256, lds, s>>>(p, b); break;
-    case 7: k_refit<7><<<grid, 256, lds, s>>>(p, b); break;
+    case 0: k_refit<0><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 1: k_refit<1><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 2: k_refit<2><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 3: k_refit<3><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 6: k_refit<6><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 7: k_refit<7><<<grid, 256, lds, s>>>(p, b, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s)
+hipError_t launch_fit(const Params &p, const BatchArgs &b, hipStream_t s, const Stamp &st)
 {
-    if (b.total_tracks <= 0) return hipSuccess;
+    if (b.total_tracks <= 0) return launch_stamp(st, s);
     const unsigned grid = blocks_for(b.total_tracks, 256);
     const size_t lds = 4 * sizeof(int) * (size_t)fit_lds_words(p.n_layers);
     switch (p.geo | (p.update3d ? 4 : 0)) {
-    case 0: k_fit<0><<<grid, 256, lds, s>>>(p, b); break;
-    case 1: k_fit<1><<<grid, 256, lds, s>>>(p, b); break;
-    case 2: k_fit<2><<<grid, 256, lds, s>>>(p, b); break;
-    case 3: k_fit<3><<<grid, 256, lds, s>>>(p, b); break;
-    case 6: k_fit<6><<<grid, 256, lds, s>>>(p, b); break;
-    case 7: k_fit<7><<<grid, 256, lds, s>>>(p, b); break;
+    case 0: k_fit<0><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 1: k_fit<1><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 2: k_fit<2><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 3: k_fit<3><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 6: k_fit<6><<<grid, 256, lds, s>>>(p, b, st); break;
+    case 7: k_fit<7><<<grid, 256, lds, s>>>(p, b, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

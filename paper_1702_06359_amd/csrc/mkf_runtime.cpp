@@ -456,22 +456,36 @@ unsigned long long *timer_close(mkf_ctx *ctx, int which, hipStream_t s, long lon
     return t.stop + slot;
 }
 
+// The stamp due, for a launch that writes it; stamp_now() for where none will.
+Stamp take_stamp(mkf_ctx *ctx)
+{
+    const Stamp st = ctx->stamp_due;
+    ctx->stamp_due = Stamp{};
+    return st;
+}
+
+void stamp_now(mkf_ctx *ctx) { (void)launch_stamp(take_stamp(ctx), ctx->stream); }
+
 void timer_begin(mkf_ctx *ctx, int which, hipStream_t s)
 {
-    if (unsigned long long *a = timer_open(ctx, which, s)) (void)launch_stamp(a, nullptr, s);
+    stamp_now(ctx);
+    ctx->stamp_due.a = timer_open(ctx, which, s);
 }
 
 void timer_end(mkf_ctx *ctx, int which, hipStream_t s, long long launches)
 {
-    if (unsigned long long *a = timer_close(ctx, which, s, launches)) (void)launch_stamp(a, nullptr, s);
+    stamp_now(ctx);
+    ctx->stamp_due.a = timer_close(ctx, which, s, launches);
 }
 
 // one phase ends, another begins
 void timer_switch(mkf_ctx *ctx, int from, int to, hipStream_t s, long long launches)
 {
+    stamp_now(ctx);
     unsigned long long *b = timer_open(ctx, to, s);   // first: it may collect
     unsigned long long *a = timer_close(ctx, from, s, launches);
-    if (a && b) (void)launch_stamp(a, b, s);
+    if (a) ctx->stamp_due = Stamp{a, b};
+    else ctx->stamp_due.a = b;
 }
 
 // Adds the recorded intervals to the totals: all of them (waiting for the
@@ -1047,7 +1061,7 @@ void set_field(DeliverJob &j, int f, void *p)
     }
 }
 
-void *device_writable(void *p, size_t bytes, size_t align, int device)
+void *device_writable(void *p, size_t bytes, size_t align, int device, char **host, size_t *range, char **dev)
 {
     if (reinterpret_cast<uintptr_t>(p) % align) return nullptr;
     hipPointerAttribute_t a{};
@@ -1064,7 +1078,13 @@ void *device_writable(void *p, size_t bytes, size_t align, int device)
         return nullptr;
     }
     const size_t off = static_cast<char *>(a.devicePointer) - static_cast<char *>(base);
-    return off <= size && bytes <= size - off ? a.devicePointer : nullptr;
+    if (off > size || bytes > size - off) return nullptr;
+    if (host) {   // the whole allocation
+        *host = static_cast<char *>(p) - off;
+        *dev = static_cast<char *>(base);
+        *range = size;
+    }
+    return a.devicePointer;
 }
 
 // Page-locked staging of at least `bytes` (contents undefined when it grows).
@@ -1126,7 +1146,7 @@ class Delivery {
             void *p = field_of(o.out, f);
             if (!p) continue;
             any = true;
-            r.direct[f] = device_writable(p, field_bytes(f, nl) * o.n, f < kOutDoubles ? 8 : 4, ctx_->device);
+            r.direct[f] = writable(static_cast<char *>(p), field_bytes(f, nl) * o.n, f < kOutDoubles ? 8 : 4);
             if (!r.direct[f]) r.staged += field_bytes(f, nl);
         }
         if (!any) return;
@@ -1135,6 +1155,21 @@ class Delivery {
         for (int f = 0; f < kOutFields; ++f)
             if (r.direct[f]) link_bytes_ += (double)field_bytes(f, nl) * o.n;
         rows_.push_back(r);
+    }
+
+    // The rows of a batch's events, added by collect(): once the launches that
+    // do not need to know of them are queued.
+    void later(EventRec *const *recs, int n, const mkf_tracks *outs)
+    {
+        recs_ = recs;
+        n_recs_ = outs ? n : 0;
+        outs_ = outs;
+    }
+    void collect()
+    {
+        for (int i = 0; i < n_recs_; ++i)
+            add(OutRows{recs_[i]->view.out_rec, recs_[i]->view.out_hits, recs_[i]->shape.n_seeds, outs_[i]});
+        n_recs_ = 0;
     }
 
     // Rows [first, end) of the rows added, in their order.
@@ -1162,8 +1197,10 @@ class Delivery {
 
     mkf_status finish()
     {
+        collect();
         mkf_status st = place(placed_, total_);
         if (st != MKF_OK || (st = launch()) != MKF_OK) return st;
+        stamp_now(ctx_);   // of a phase that nothing was launched after
         if (n_slots_ > 1) {
             if ((st = mark_slot()) != MKF_OK) return st;
             for (int k = 1; k <= n_slots_; ++k)   // oldest first
@@ -1210,6 +1247,19 @@ class Delivery {
         return MKF_OK;
     }
 
+    // device_writable(), asked once for each allocation that this call's arrays
+    // lie in
+    void *writable(char *p, size_t bytes, size_t align)
+    {
+        if (reinterpret_cast<uintptr_t>(p) % align) return nullptr;
+        for (const Range &r : ranges_)
+            if (p >= r.host && p + bytes <= r.host + r.bytes) return r.dev + (p - r.host);
+        Range r{};
+        void *dev = device_writable(p, bytes, align, ctx_->device, &r.host, &r.bytes, &r.dev);
+        if (dev && r.host) ranges_.push_back(r);
+        return dev;
+    }
+
     // jobs for the rows of r: all at once, or as many as a slot still holds
     mkf_status place_rows(const Rows &r, int r0, int r1)
     {
@@ -1252,7 +1302,7 @@ class Delivery {
     mkf_status launch()
     {
         if (args_.n_jobs == 0) return MKF_OK;
-        MKF_HIP(launch_deliver(args_, ctx_->stream));
+        MKF_HIP(launch_deliver(args_, ctx_->stream, take_stamp(ctx_)));
         launched();
         return MKF_OK;
     }
@@ -1306,7 +1356,15 @@ class Delivery {
     mkf_ctx *ctx_;
     const bool fixed_;
     DeliverArgs args_;
+    struct Range {
+        char *host, *dev;
+        size_t bytes;
+    };
+    std::vector<Range> ranges_;
     std::vector<Rows> rows_;
+    EventRec *const *recs_ = nullptr;
+    const mkf_tracks *outs_ = nullptr;
+    int n_recs_ = 0;
     size_t staged_ = 0, slot_bytes_ = 0, used_ = 0;
     double link_bytes_ = 0.0;
     long long total_ = 0, placed_ = 0;
@@ -1395,16 +1453,17 @@ mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, cons
     if (stats) MKF_HIP(launch_batch_zero(args, s));
     if (reindex) {
         if (timed) timer_begin(ctx, 1, s);
-        MKF_HIP(launch_index(P, args, s));
+        MKF_HIP(launch_index(P, args, s, timed ? take_stamp(ctx) : Stamp{}));
     }
     if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
     if (timed && reindex) timer_switch(ctx, 1, 0, s, 1);   // one index build of the batch
     else if (timed) timer_begin(ctx, 0, s);
+    if (d) d->collect();
     std::vector<long long> ends{0};   // one part, however many rows
     if (d && !t.persistent) ends = plan_parts(loads, P, d->us_per_row());
     if (ends.size() == 1) {
         MKF_HIP(launch_build_batch(P, args, t.lanes_per_seed, t.waves_per_block, t.persistent,
-                                   ctx->n_cu * t.blocks_per_cu, stats, nullptr, s));
+                                   ctx->n_cu * t.blocks_per_cu, stats, nullptr, s, timed ? take_stamp(ctx) : Stamp{}));
     } else {
         BatchArgs part = args;
         long long at = 0;
@@ -1419,13 +1478,14 @@ mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, cons
                 jobs = ctx->build_jobs + k;
                 *jobs = d->pending();
             }
-            MKF_HIP(launch_build_batch(P, part, t.lanes_per_seed, t.waves_per_block, 0, 0, stats, jobs, s));
+            MKF_HIP(launch_build_batch(P, part, t.lanes_per_seed, t.waves_per_block, 0, 0, stats, jobs, s,
+                                       timed && k == 0 ? take_stamp(ctx) : Stamp{}));
             if (k) d->launched();
         }
     }
     if (flags & MKF_BATCH_FIT) {
         if (timed) timer_switch(ctx, 0, 2, s, 1);
-        MKF_HIP(launch_refit(P, args, s));
+        MKF_HIP(launch_refit(P, args, s, timed ? take_stamp(ctx) : Stamp{}));
         if (timed) timer_end(ctx, 2, s, 1);
     } else if (timed) {
         timer_end(ctx, 0, s, 1);
@@ -1761,6 +1821,7 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
             rec->plain_graph_wpb = wpb;
         }
         timer_begin(ctx, 0, ctx->stream);
+        stamp_now(ctx);
         MKF_HIP(hipGraphLaunch(rec->plain_graph, ctx->stream));
         timer_end(ctx, 0, ctx->stream, n_launch);
     }
@@ -1796,7 +1857,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
     if (need_index) flags |= MKF_BATCH_REINDEX;
     std::unique_ptr<Delivery> d;   // none for an asynchronous batch: its destructor waits
     if (!async) d = std::make_unique<Delivery>(ctx);
-    for (int i = 0; outs && i < n; ++i) d->add(build_rows(recs[i], outs[i]));
+    if (d) d->later(recs.data(), n, outs);
     const int spi = seeds_per_item(ctx->params.geo, ctx->tuning.lanes_per_seed, recs.data(), n);
     if (flags & MKF_BATCH_GRAPH) {
         BatchGraph *bg = nullptr;
@@ -1844,6 +1905,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
             ctx->graphs.push_back(std::move(g));
         }
         timer_begin(ctx, 0, ctx->stream);
+        stamp_now(ctx);
         MKF_HIP(hipGraphLaunch(bg->exec, ctx->stream));
         timer_end(ctx, 0, ctx->stream, 1);
     } else {
@@ -1856,6 +1918,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
             return st;
     }
     if (async) {
+        stamp_now(ctx);
         timers_collect(ctx, false);
         return MKF_OK;
     }
@@ -1911,11 +1974,12 @@ mkf_status mkf_build_batch_noalloc(mkf_ctx *ctx, const int32_t *handles, int32_t
     }
     std::unique_ptr<Delivery> d;
     if (!async) d = std::make_unique<Delivery>(ctx, true);
-    for (int i = 0; outs && i < n; ++i) d->add(build_rows(recs[i], outs[i]));
+    if (d) d->later(recs, n, outs);
     mkf_status st = run_pipeline(ctx, ctx->params, ctx->tuning, args, flags, true, ctx->stream, d.get(),
                                  event_loads(recs, n));
     if (st != MKF_OK) return st;
     if (async) {
+        stamp_now(ctx);
         timers_collect(ctx, false);
         return MKF_OK;
     }
@@ -2033,7 +2097,7 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, 64, &args, ctx->stream)) != MKF_OK)
         return st;
     timer_begin(ctx, 2, ctx->stream);
-    MKF_HIP(launch_fit(ctx->params, args, ctx->stream));
+    MKF_HIP(launch_fit(ctx->params, args, ctx->stream, take_stamp(ctx)));
     timer_end(ctx, 2, ctx->stream, 1);
     Delivery d(ctx);
     for (int i = 0; outs && i < n; ++i)
@@ -2112,7 +2176,7 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     BatchArgs args{};
     if ((st = stage_batch(ctx, one, ctx->batch_dev, ctx->batch_host, 64, &args, s)) != MKF_OK) return cleanup(st);
     timer_begin(ctx, 2, s);
-    hipError_t e = launch_fit(ctx->params, args, s);
+    hipError_t e = launch_fit(ctx->params, args, s, take_stamp(ctx));
     timer_end(ctx, 2, s, 1);
     if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit launch: %s", hipGetErrorString(e)));
     {

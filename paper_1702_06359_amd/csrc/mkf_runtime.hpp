@@ -107,9 +107,9 @@ struct BatchGraph {
 // Device time of the timed phases: a ring of (start, stop) wall-clock stamps
 // in page-locked memory, so that calls that return before the device finishes
 // (asynchronous batches) each keep their own interval until it is collected.
-// The stamps are written by a one-thread kernel in the stream: 1.5 us each,
-// where a pair of HIP events around a kernel adds 5.6-6.5 us to a call.  A
-// phase that ends where the next begins shares its stamp.
+// The stamps are written by the launch that begins a phase or follows its end,
+// or by a one-thread kernel in the stream where none does: 1.5-4.5 us, where a
+// pair of HIP events around a kernel adds 5.6-6.5 us to a call.
 struct Timer {
     static constexpr int kRing = 32;
     unsigned long long *start = nullptr, *stop = nullptr;   // kRing each; 0: not written yet
@@ -194,6 +194,7 @@ struct mkf_ctx {
     std::vector<std::unique_ptr<mkf::BatchGraph>> graphs;
     mkf::Timer timers[3];
     unsigned long long *stamps = nullptr;       // their rings, page-locked
+    mkf::Stamp stamp_due;                       // of the next launch on the context's stream
     double ms_per_tick = 0.0;
     std::unique_ptr<mkf::Server, mkf::ServerDeleter> server;
 };
@@ -258,8 +259,9 @@ void *field_of(const mkf_tracks &t, int f);
 void set_field(DeliverJob &j, int f, void *p);
 // the device's address of `bytes` of host memory at p when all of it is
 // page-locked for this device (or device memory of it) and p a multiple of
-// `align`, else null
-void *device_writable(void *p, size_t bytes, size_t align, int device);
+// `align`, else null; with `host`, the allocation it lies in too
+void *device_writable(void *p, size_t bytes, size_t align, int device, char **host = nullptr, size_t *range = nullptr,
+                      char **dev = nullptr);
 void shutdown_server(mkf_ctx *ctx);
 
 }  // namespace mkf
