@@ -1358,10 +1358,16 @@ constexpr int kRecLds = kRecWords + 1;
 // field as one contiguous run, eight bytes a lane, so that the link carries
 // whole 64-byte pieces whatever the field.
 // `t`: kWave * kRecLds words of the wavefront's own; it takes every `step`-th
-// tile from `first` on.
-template <class Args>
-__device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first, int step, int lane)
+// tile from `first` on.  kSplit > 1: of a block of kSplit wavefronts that move
+// a tile together, the `part`-th.
+template <int kSplit, class Args>
+__device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first, int step, int lane, int part)
 {
+    static_assert(kSplit == 1 || kSplit == 4, "a wavefront, or four: state and counts, three thirds of the covariance");
+    auto sync = [] {
+        if constexpr (kSplit > 1) __syncthreads();
+        else wave_lds_sync();
+    };
     int j = 0;
     for (int tile = uniform(first); tile < A.n_tiles; tile += step) {
         while (j + 1 < A.n_jobs && A.job[j + 1].first_tile <= tile) ++j;
@@ -1369,34 +1375,37 @@ __device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first
         const size_t r0 = (size_t)(tile - J.first_tile) * kDeliverTile;
         const int m = min(kDeliverTile, J.n - (int)r0);
         const float4 *src = reinterpret_cast<const float4 *>(J.rec + r0 * kRecWords);
-        float4 v[kRecWords / 4];
+        constexpr int kLoads = kRecWords / 4 / kSplit;
+        float4 v[kLoads];
 #pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k) {
-            const int w = k * kWave + lane;
+        for (int k = 0; k < kLoads; ++k) {
+            const int w = (k * kSplit + part) * kWave + lane;
             v[k] = (w >> 3) < m ? load_global(src + w) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k) {
-            const int w = k * kWave + lane;
+        for (int k = 0; k < kLoads; ++k) {
+            const int w = (k * kSplit + part) * kWave + lane;
             float *q = t + kRecLds * (w >> 3) + 4 * (w & 7);
             q[0] = v[k].x; q[1] = v[k].y; q[2] = v[k].z; q[3] = v[k].w;
         }
-        wave_lds_sync();
-        if (J.par) {
+        sync();
+        if (J.par && part == 0) {
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
                 const int w = k * kWave + lane, row = w / 6;
                 if (row < m) store_global(J.par + r0 * 6 + w, (double)t[kRecLds * row + w - 6 * row]);
             }
         }
-        if (J.cov) {
+        if (J.cov && (kSplit == 1 || part > 0)) {
+            constexpr int kStores = kSplit == 1 ? 21 : 7;
+            const int k0 = kSplit == 1 ? 0 : (part - 1) * kStores;
 #pragma unroll
-            for (int k = 0; k < 21; ++k) {
-                const int w = k * kWave + lane, row = w / 21;
+            for (int k = 0; k < kStores; ++k) {
+                const int w = (k0 + k) * kWave + lane, row = w / 21;
                 if (row < m) store_global(J.cov + r0 * 21 + w, (double)t[kRecLds * row + kRecCov + w - 21 * row]);
             }
         }
-        if (lane < m) {
+        if (part == 0 && lane < m) {
             const float *row = t + kRecLds * lane;
             const size_t r = r0 + lane;
             const int nh = __float_as_int(row[kRecHits]), st = __float_as_int(row[kRecStatus]);
@@ -1410,22 +1419,28 @@ __device__ __forceinline__ void deliver_tiles(const Args &A, float *t, int first
         if (J.hits_out) {
             const int n = m * A.n_layers;
             const int *src_h = J.hits + r0 * A.n_layers;
-            for (int w = lane; w < n; w += kWave) store_global(J.hits_out + r0 * A.n_layers + w, load_global(src_h + w));
+            for (int w = part * kWave + lane; w < n; w += kSplit * kWave)
+                store_global(J.hits_out + r0 * A.n_layers + w, load_global(src_h + w));
         }
-        wave_lds_sync();   // every row read before the next tile takes its place
+        sync();   // every row read before the next tile takes its place
     }
 }
 
 constexpr int kDeliverLds = kWave * kRecLds * (int)sizeof(float);   // per wavefront
 
-template <int kJobs>
+template <int kJobs, int kSplit>
 __global__ void __launch_bounds__(256) k_deliver(const DeliverArgsT<kJobs> A, const Stamp st)
 {
     extern __shared__ int s_dyn[];
     stamp_start(st);
-    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    deliver_tiles(A, reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
-                  blockIdx.x * waves + wave, gridDim.x * waves, threadIdx.x & (kWave - 1));
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    float *t = reinterpret_cast<float *>(s_dyn);
+    if constexpr (kSplit > 1) {
+        deliver_tiles<kSplit>(A, t, blockIdx.x, gridDim.x, lane, wave);
+    } else {
+        deliver_tiles<1>(A, t + wave * (kDeliverLds / (int)sizeof(float)), blockIdx.x * waves + wave,
+                         gridDim.x * waves, lane, 0);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1464,8 +1479,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
         if (x == 0) {
             typedef const __attribute__((address_space(4))) DeliverArgs CDeliver;
             if (i < deliver_blocks)
-                deliver_tiles(*(CDeliver *)D, reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
-                              i * W + wave, deliver_blocks * W, lane);
+                deliver_tiles<1>(*(CDeliver *)D,
+                                 reinterpret_cast<float *>(s_dyn) + wave * (kDeliverLds / (int)sizeof(float)),
+                                 i * W + wave, deliver_blocks * W, lane, 0);
             return;
         }
         const int n = (B.end_item - B.first_item + W - 1) / W;   // building blocks
@@ -1518,20 +1534,29 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(geo_xy
     if (L == P.n_seed_layers) {
         init_lane(S, E, P, valid ? seed : 0, valid && lane % G == 0);
     } else {
+        // every lane's words in flight together, a dead one's (whatever its slot
+        // holds) dropped after: loads that wait for `meta` made a layer of a
+        // small event 0.8 us longer
         const int meta = load_global(E.st_meta + slot);
+        const float chi2 = load_global(E.st_chi2 + slot);
+        float p[6], c[21], tg[4];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) p[i] = load_global(E.st_par + i * ns + slot);
+#pragma unroll
+        for (int i = 0; i < 21; ++i) c[i] = load_global(E.st_cov + i * ns + slot);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tg[i] = load_global(E.st_trig + i * ns + slot);
         S.live = meta & 1;
         S.stopped = (meta >> 1) & 1;
         S.status = (meta >> 2) & 3;
         S.n_hits = (meta >> 4) & 31;
         S.n_holes = (meta >> 9) & 15;
-        S.chi2 = load_global(E.st_chi2 + slot);
+        S.chi2 = chi2;
 #pragma unroll
-        for (int i = 0; i < 6; ++i) S.p[i] = S.live ? load_global(E.st_par + i * ns + slot) : 0.f;
+        for (int i = 0; i < 6; ++i) S.p[i] = S.live ? p[i] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 21; ++i) S.c[i] = S.live ? load_global(E.st_cov + i * ns + slot) : 0.f;
-        S.tg = S.live ? Trig{load_global(E.st_trig + 0 * ns + slot), load_global(E.st_trig + 1 * ns + slot),
-                             load_global(E.st_trig + 2 * ns + slot), load_global(E.st_trig + 3 * ns + slot)}
-                      : Trig{0.f, 1.f, 1.f, 0.f};
+        for (int i = 0; i < 21; ++i) S.c[i] = S.live ? c[i] : 0.f;
+        S.tg = S.live ? Trig{tg[0], tg[1], tg[2], tg[3]} : Trig{0.f, 1.f, 1.f, 0.f};
     }
     extern __shared__ int s_dyn[];
     SearchLds<kGeo> &SL = reinterpret_cast<SearchLds<kGeo> *>(s_dyn)[threadIdx.x >> 6];
@@ -2002,8 +2027,9 @@ constexpr int kFewJobs = 2;
 template <int kJobs>
 static hipError_t launch_deliver_t(const DeliverArgsT<kJobs> &a, const Stamp &st, hipStream_t s)
 {
-    if (a.n_tiles <= kDeliverWaves) k_deliver<kJobs><<<a.n_tiles, kWave, kDeliverLds, s>>>(a, st);
-    else k_deliver<kJobs><<<kDeliverWaves / 4, 4 * kWave, 4 * kDeliverLds, s>>>(a, st);
+    if (a.n_tiles <= kDeliverWaves / 4) k_deliver<kJobs, 4><<<a.n_tiles, 4 * kWave, kDeliverLds, s>>>(a, st);
+    else if (a.n_tiles <= kDeliverWaves) k_deliver<kJobs, 1><<<a.n_tiles, kWave, kDeliverLds, s>>>(a, st);
+    else k_deliver<kJobs, 1><<<kDeliverWaves / 4, 4 * kWave, 4 * kDeliverLds, s>>>(a, st);
     return hipGetLastError();
 }
 
