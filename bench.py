@@ -38,8 +38,8 @@ FLOP_PER_UPDATE = 187         # gain, state and covariance update
 FLOP_PER_UPDATE_JOSEPH = 445  # fit update in Joseph form (the first JOSEPH_UPDATES of a fit)
 JOSEPH_UPDATES = 3
 FLOP_PER_FIT_STEP = FLOP_SCATTER + FLOP_PROPAGATE + FLOP_TRANSPORT   # 388, layers 1..9 of a fit
-BYTES_PER_FIT_TRACK = 108 + 40 + 10 * 16 + 232   # prior (f32), hit ids, hits (float4), fit result (f64)
-BYTES_PER_SEED_IO = 120 + 276     # seed in (f32 state, cov, hit ids) + track out (f64)
+BYTES_PER_FIT_TRACK = 108 + 40 + 10 * 16 + 128   # prior (f32), hit ids, hits (float4), result row (f32)
+BYTES_PER_SEED_IO = 124 + 168     # seed in (f32 state, cov, hit ids, order) + result row and hit list out (f32)
 BYTES_PER_HIT = 16                # binned hit read once
 BYTES_PER_BIN = 4                 # bin offset read once
 PEAK_FP32_VALU_TFLOPS = 157.3     # MI355X vector FP32 (256 CU x 2.4 GHz x 256 FLOP/clk)

@@ -130,7 +130,8 @@ typedef struct {
 } mkf_event;
 
 /* Track output, caller-allocated, one row per seed (building) or per track
- * (fitting).  Any pointer may be NULL to skip that field.
+ * (fitting).  Any pointer may be NULL to skip that field.  Page-locked arrays
+ * are written by the device directly, others through the library's staging.
  *  par  [n][6], cov [n][21]: state and covariance on the last surface the
  *        candidate reached (building) or after the last update (fitting);
  *        scattering of that last surface is not included.
@@ -227,8 +228,9 @@ mkf_status mkf_load_event(mkf_ctx *ctx, const mkf_event *ev, int32_t *handle);
 /* Load n events at once: as mkf_load_event for each, with their copies and
  * their hit indices in one pass and one wait (Section 5: on a GPU the setup
  * copies dominate).  The inputs are checked and narrowed to FP32 on up to
- * 16 host threads into pinned staging (12 bytes per hit, 120 per seed),
- * then copied in one piece per event.  handles[n] receives the handles.  On
+ * 16 host threads into pinned staging (16 bytes per hit, 124 per seed),
+ * each part copied as it is packed: the hits, then, while their index is
+ * built, the seeds and tracks.  handles[n] receives the handles.  On
  * error nothing is loaded and the message names the failing event.  At most
  * 65,535 / n_layers events per call. */
 mkf_status mkf_load_events(mkf_ctx *ctx, const mkf_event *evs, int32_t n, int32_t *handles);
@@ -345,11 +347,11 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
  * one launch.  outs: n entries (outs[i].n = that event's n_tracks) or NULL. */
 mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tracks *outs);
 
-/* Device time of the library's kernels, from HIP events recorded on the
- * context stream around each launch of non-graph calls (waits for the
- * stream first).  which: 0 = build
- * (batched build kernel, or the plain per-layer kernels), 1 = hit index
- * (one count per index build of a batch), 2 = fit.  Returns the summed
+/* Device time of the library's kernels, from the device's clock at the start
+ * and the end of each phase on the context stream (waits for the stream
+ * first).  which: 0 = build (the batched build, with what it delivers to the
+ * host on the way, or the plain per-layer kernels), 1 = hit index (one count
+ * per index build of a batch), 2 = fit.  Returns the summed
  * milliseconds and launch count since the last reset. */
 mkf_status mkf_timer_read(mkf_ctx *ctx, int32_t which, double *total_ms, int64_t *launches);
 mkf_status mkf_timer_reset(mkf_ctx *ctx);
@@ -381,7 +383,9 @@ mkf_status mkf_autotune(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tun
 /* Configure serving: device-memory budget in bytes (reserved at once, a
  * slab that admitted events are placed in), events in flight (submitted and
  * not finished), events per batched build (0 = all that are waiting).  Also
- * allocates, outside the budget, the batch descriptors of each stream.
+ * allocates, outside the budget, the batch descriptors of each stream and
+ * page-locked staging for inputs and results (up to 64 MiB, no more than the
+ * budget).
  * Errors: MKF_E_INVALID, MKF_E_NOMEM (the budget cannot be reserved),
  * MKF_E_STATE (tickets of a previous configuration still in flight),
  * MKF_E_DEVICE. */
