@@ -1122,7 +1122,9 @@ static size_t out_pin_bytes(size_t rows, size_t sets, int n_layers)
 // with 8 threads, 389 with one; fitted tracks of 8 x 5,000: 1,023 and 809).
 class Delivery {
   public:
-    // fixed: no allocation, whatever staging the context has is used
+    // fixed: no allocation, whatever staging the context has is used (a load of
+    // small events leaves less than a tile's: then the kOutLeast made with the
+    // context)
     explicit Delivery(mkf_ctx *ctx, bool fixed = false) : ctx_(ctx), fixed_(fixed)
     {
         args_.n_jobs = args_.n_tiles = 0;
@@ -1235,14 +1237,13 @@ class Delivery {
         if (!staged_) return MKF_OK;
         mkf_status st;
         const size_t need = out_need_bytes(staged_, rows_.size());
-        const size_t least = 64 << 10;   // a tile of rows and more
-        if ((!fixed_ || ctx_->load_pin_bytes < least) &&
-            (st = ensure_pin(ctx_, std::min(need, kOutSlots * kOutSlotMax))) != MKF_OK)
-            return st;
+        if (!fixed_ && (st = ensure_pin(ctx_, std::min(need, kOutSlots * kOutSlotMax))) != MKF_OK) return st;
+        const bool small = ctx_->load_pin_bytes < std::min(need, kOutLeast);   // only when fixed
+        stage_ = small ? ctx_->least_pin : static_cast<char *>(ctx_->load_pin);
         // equal slots for everything where the staging holds it, else a ring
-        const size_t have = std::min(need, ctx_->load_pin_bytes);
+        const size_t have = std::min(need, small ? kOutLeast : ctx_->load_pin_bytes);
         n_slots_ = have < need ? kOutSlots : (int)std::min<size_t>(kOutSlots, std::max<size_t>(1, need / kOutSlotMin));
-        if (have / n_slots_ < least) n_slots_ = 1;
+        if (have / n_slots_ < kOutLeast) n_slots_ = 1;
         slot_bytes_ = have / n_slots_ & ~size_t(255);
         return MKF_OK;
     }
@@ -1288,7 +1289,7 @@ class Delivery {
                 if (r.direct[f]) {
                     set_field(j, f, static_cast<char *>(r.direct[f]) + fb * r0);
                 } else {
-                    char *stage = static_cast<char *>(ctx_->load_pin) + cur_ * slot_bytes_ + used_;
+                    char *stage = stage_ + cur_ * slot_bytes_ + used_;
                     used_ += (fb * m + 255) & ~size_t(255);
                     set_field(j, f, stage);
                     slot_[cur_].copies.push_back(HostCopy{p + fb * r0, stage, fb * m});
@@ -1365,6 +1366,7 @@ class Delivery {
     EventRec *const *recs_ = nullptr;
     const mkf_tracks *outs_ = nullptr;
     int n_recs_ = 0;
+    char *stage_ = nullptr;
     size_t staged_ = 0, slot_bytes_ = 0, used_ = 0;
     double link_bytes_ = 0.0;
     long long total_ = 0, placed_ = 0;
@@ -1578,11 +1580,12 @@ mkf_status mkf_create(const mkf_config *cfg, const mkf_allocator *alloc, void *h
     ctx->ms_per_tick = 1.0 / khz;
     constexpr size_t kStampBytes = 3 * 2 * Timer::kRing * sizeof(unsigned long long);
     constexpr size_t kJobBytes = kBuildParts * sizeof(DeliverArgs), kMarkBytes = kOutSlots * sizeof(unsigned);
-    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), kStampBytes + kJobBytes + kMarkBytes,
-                          hipHostMallocDefault));
+    constexpr size_t kWords = round_up_256(kStampBytes + kJobBytes + kMarkBytes);
+    MKF_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->stamps), kWords + kOutLeast, hipHostMallocDefault));
     ctx->build_jobs = reinterpret_cast<DeliverArgs *>(reinterpret_cast<char *>(ctx->stamps) + kStampBytes);
     ctx->out_marks = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(ctx->build_jobs) + kJobBytes);
     std::memset(ctx->out_marks, 0, kMarkBytes);
+    ctx->least_pin = reinterpret_cast<char *>(ctx->stamps) + kWords;
     for (int k = 0; k < 3; ++k) {
         ctx->timers[k].start = ctx->stamps + (2 * k) * Timer::kRing;
         ctx->timers[k].stop = ctx->stamps + (2 * k + 1) * Timer::kRing;
@@ -1606,7 +1609,7 @@ void mkf_destroy(mkf_ctx *ctx)
     ctx->heap.release(ctx->batch_dev);
     if (ctx->batch_host) (void)hipHostFree(ctx->batch_host);
     if (ctx->load_pin) (void)hipHostFree(ctx->load_pin);
-    if (ctx->stamps) (void)hipHostFree(ctx->stamps);   // and the build jobs and marks behind them
+    if (ctx->stamps) (void)hipHostFree(ctx->stamps);   // and the build jobs, marks and staging behind them
     if (ctx->stage_done) (void)hipEventDestroy(ctx->stage_done);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

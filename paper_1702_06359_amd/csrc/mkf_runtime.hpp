@@ -148,6 +148,7 @@ struct HostCopy {   // staged bytes to copy once the device has written them
 constexpr int kOutSlots = 4;
 constexpr int kBuildParts = 8;   // parts a batch with host outputs is built in, at most
 constexpr size_t kOutSlotMin = size_t(512) << 10, kOutSlotMax = size_t(4) << 20;
+constexpr size_t kOutLeast = size_t(64) << 10;   // the smallest staging used: a tile of rows and more
 
 struct Server;   // serving state (mkf_serve.cpp)
 struct ServerDeleter {
@@ -185,9 +186,11 @@ struct mkf_ctx {
     std::vector<char> staged_image;     // what batch_dev holds (empty: unknown)
     // pinned staging of the packed inputs of loads and fits on their way in and
     // of results on their way out; every call that uses it ends waiting for
-    // the stream, so it is free at the start of the next
+    // all that it queued to have passed through it, so it is free at the start
+    // of the next
     void *load_pin = nullptr;
     size_t load_pin_bytes = 0;
+    char *least_pin = nullptr;                      // page-locked, kOutLeast: for a call that may not make load_pin larger
     mkf::DeliverArgs *build_jobs = nullptr;         // page-locked: rows that build launches of the current call deliver
     unsigned *out_marks = nullptr;                  // page-locked: one a slot of the result staging (k_mark)
     unsigned out_mark = 0;                          // the last value used
