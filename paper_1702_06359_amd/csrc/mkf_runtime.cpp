@@ -706,7 +706,7 @@ static long long pack_states(const double *par, const double *cov, const int32_t
             ohits[i * n_hit_layers + L] = h;
         }
     if (ok && !out) return -1;
-    for (size_t i = 0; i < n; ++i) {
+    for (size_t i = 0; i < n; ++i) {   // the first that failed
         if (!narrow_all(par + 6 * i, fpar + 6 * i, 6) || !narrow_all(cov + 21 * i, fcov + 21 * i, 21) ||
             !states_in_range(par + 6 * i, 1))
             return (long long)i;
@@ -718,7 +718,7 @@ static long long pack_states(const double *par, const double *cov, const int32_t
             }
         }
     }
-    return -1;
+    return 0;   // what was refused once stays refused, whatever a second look says
 }
 
 // Packs an event's inputs into `image` in the device layout of its data
@@ -777,11 +777,13 @@ mkf_status pack_event(const mkf_event *ev, const EventShape &sh, int geo, void *
             const size_t n = (size_t)ev->n_hits[t];
             float *o = reinterpret_cast<float *>(const_cast<float4 *>(v.hits) + sh.layer_off[t]);
             if (pack_hits(ev->hit_xyz[t], n, form, o)) return;
+            bad[t] = 0;   // what was refused once stays refused, whatever a second look says
             for (size_t i = 0; i < n; ++i)   // the first that failed
                 if (!pack_hits(ev->hit_xyz[t] + 3 * i, 1, form, o + 4 * i)) {
                     bad[t] = (int)i;
-                    return;
+                    break;
                 }
+            return;
         }
         const bool seeds = t < nl + seed_tasks;
         const size_t i0 = (size_t)(seeds ? t - nl : t - nl - seed_tasks) * chunk;
