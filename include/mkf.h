@@ -349,7 +349,9 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
 
 /* Device time of the library's kernels, from the device's clock at the start
  * and the end of each phase on the context stream (waits for the stream
- * first).  which: 0 = build (the batched build, with what it delivers to the
+ * first).  A phase ends at the launch that follows it, which is queued before
+ * the phase is done: no allocation and no look at the caller's arrays lies
+ * between.  which: 0 = build (the batched build, with what it delivers to the
  * host on the way, or the plain per-layer kernels), 1 = hit index (one count
  * per index build of a batch), 2 = fit.  Returns the summed
  * milliseconds and launch count since the last reset. */

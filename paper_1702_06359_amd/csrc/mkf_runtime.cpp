@@ -1161,7 +1161,7 @@ class Delivery {
         rows_.push_back(r);
     }
 
-    // The rows of a batch's events, added by collect(): once the launches that
+    // The rows of a batch's events, added by prepare(): once the launches that
     // do not need to know of them are queued.
     void later(EventRec *const *recs, int n, const mkf_tracks *outs)
     {
@@ -1169,18 +1169,23 @@ class Delivery {
         n_recs_ = outs ? n : 0;
         outs_ = outs;
     }
-    void collect()
+    bool expects_rows() const { return n_recs_ > 0 || !rows_.empty(); }
+
+    // What takes the host long - looking up the arrays of many events, growing
+    // the staging - before the launch whose end the delivery's will stamp, so
+    // that the phase's time holds none of it.  Nothing is added afterwards.
+    mkf_status prepare()
     {
         for (int i = 0; i < n_recs_; ++i)
             add(OutRows{recs_[i]->view.out_rec, recs_[i]->view.out_hits, recs_[i]->shape.n_seeds, outs_[i]});
         n_recs_ = 0;
+        return begun_ ? MKF_OK : begin();
     }
 
-    // Rows [first, end) of the rows added, in their order.
+    // Rows [first, end) of the rows added, in their order (after prepare()).
     mkf_status place(long long first, long long end)
     {
         mkf_status st;
-        if (!begun_ && (st = begin()) != MKF_OK) return st;
         for (const Rows &r : rows_) {
             const long long a = std::max(first - r.before, 0LL), b = std::min<long long>(end - r.before, r.o.n);
             if (a < b && (st = place_rows(r, (int)a, (int)b)) != MKF_OK) return st;
@@ -1201,9 +1206,9 @@ class Delivery {
 
     mkf_status finish()
     {
-        collect();
-        mkf_status st = place(placed_, total_);
-        if (st != MKF_OK || (st = launch()) != MKF_OK) return st;
+        mkf_status st = prepare();
+        if (st != MKF_OK || (st = place(placed_, total_)) != MKF_OK) return st;
+        if ((st = launch()) != MKF_OK) return st;
         stamp_now(ctx_);   // of a phase that nothing was launched after
         if (n_slots_ > 1) {
             if ((st = mark_slot()) != MKF_OK) return st;
@@ -1460,9 +1465,18 @@ mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, cons
         MKF_HIP(launch_index(P, args, s, timed ? take_stamp(ctx) : Stamp{}));
     }
     if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
-    if (timed && reindex) timer_switch(ctx, 1, 0, s, 1);   // one index build of the batch
-    else if (timed) timer_begin(ctx, 0, s);
-    if (d) d->collect();
+    // one index build of the batch; with rows to deliver the host has work to do
+    // before the next launch, so the index's end gets a stamp of its own
+    if (timed && reindex && !(d && d->expects_rows())) {
+        timer_switch(ctx, 1, 0, s, 1);
+    } else if (timed) {
+        if (reindex) timer_end(ctx, 1, s, 1);
+        timer_begin(ctx, 0, s);
+    }
+    if (d) {
+        const mkf_status st = d->prepare();
+        if (st != MKF_OK) return st;
+    }
     std::vector<long long> ends{0};   // one part, however many rows
     if (d && !t.persistent) ends = plan_parts(loads, P, d->us_per_row());
     if (ends.size() == 1) {
@@ -1825,14 +1839,17 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
             rec->plain_graph_G = G;
             rec->plain_graph_wpb = wpb;
         }
+        Delivery d(ctx);
+        if (out) d.add(build_rows(rec, *out));
+        if ((st = d.prepare()) != MKF_OK) return st;
         timer_begin(ctx, 0, ctx->stream);
         stamp_now(ctx);
         MKF_HIP(hipGraphLaunch(rec->plain_graph, ctx->stream));
         timer_end(ctx, 0, ctx->stream, n_launch);
+        if ((st = d.finish()) != MKF_OK) return st;
+    } else {
+        MKF_HIP(hipStreamSynchronize(ctx->stream));
     }
-    Delivery d(ctx);
-    if (out) d.add(build_rows(rec, *out));
-    if ((st = d.finish()) != MKF_OK) return st;
     timers_collect(ctx, false);   // all has run
     return MKF_OK;
 }
@@ -1909,6 +1926,7 @@ mkf_status mkf_build_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, uint
             bg = g.get();
             ctx->graphs.push_back(std::move(g));
         }
+        if (d && (st = d->prepare()) != MKF_OK) return st;
         timer_begin(ctx, 0, ctx->stream);
         stamp_now(ctx);
         MKF_HIP(hipGraphLaunch(bg->exec, ctx->stream));
@@ -2101,12 +2119,13 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     BatchArgs args{};
     if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, 64, &args, ctx->stream)) != MKF_OK)
         return st;
-    timer_begin(ctx, 2, ctx->stream);
-    MKF_HIP(launch_fit(ctx->params, args, ctx->stream, take_stamp(ctx)));
-    timer_end(ctx, 2, ctx->stream, 1);
     Delivery d(ctx);
     for (int i = 0; outs && i < n; ++i)
         d.add(OutRows{recs[i]->view.fit_rec, recs[i]->view.track_hits, recs[i]->shape.n_tracks, outs[i]});
+    if ((st = d.prepare()) != MKF_OK) return st;
+    timer_begin(ctx, 2, ctx->stream);
+    MKF_HIP(launch_fit(ctx->params, args, ctx->stream, take_stamp(ctx)));
+    timer_end(ctx, 2, ctx->stream, 1);
     if ((st = d.finish()) != MKF_OK) return st;
     timers_collect(ctx, false);   // all has run
     return MKF_OK;
@@ -2180,13 +2199,14 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     std::vector<EventRec *> one{&tmp};
     BatchArgs args{};
     if ((st = stage_batch(ctx, one, ctx->batch_dev, ctx->batch_host, 64, &args, s)) != MKF_OK) return cleanup(st);
-    timer_begin(ctx, 2, s);
-    hipError_t e = launch_fit(ctx->params, args, s, take_stamp(ctx));
-    timer_end(ctx, 2, s, 1);
-    if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit launch: %s", hipGetErrorString(e)));
     {
         Delivery d(ctx);
         if (out) d.add(OutRows{v.fit_rec, v.track_hits, n_tracks, *out});
+        if ((st = d.prepare()) != MKF_OK) return cleanup(st);
+        timer_begin(ctx, 2, s);
+        const hipError_t e = launch_fit(ctx->params, args, s, take_stamp(ctx));
+        timer_end(ctx, 2, s, 1);
+        if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit launch: %s", hipGetErrorString(e)));
         if ((st = d.finish()) != MKF_OK) return cleanup(st);
     }
     timers_collect(ctx, false);   // all has run
