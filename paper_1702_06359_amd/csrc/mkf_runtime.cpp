@@ -433,11 +433,15 @@ mkf_status check_tuning(const mkf_config &c, mkf_tuning *t)
 
 void timers_collect(mkf_ctx *ctx, bool wait);
 
-// Opens an interval; returns where its start stamp goes (null: not timed).
+// Opens an interval; returns where its start stamp goes (null: not timed, as
+// under a capture by the caller: the launches do not run now, and replays of
+// them would stamp the ring's words while other calls use them).
 unsigned long long *timer_open(mkf_ctx *ctx, int which, hipStream_t s)
 {
     Timer &t = ctx->timers[which];
-    if (s != ctx->stream) return nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (s != ctx->stream || hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+        return nullptr;
     if (t.count == Timer::kRing) timers_collect(ctx, true);
     const int slot = (t.head + t.count) % Timer::kRing;
     t.start[slot] = t.stop[slot] = 0;

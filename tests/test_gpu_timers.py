@@ -74,3 +74,36 @@ def test_a_growing_staging_is_no_part_of_a_phase(gpu_required, path):
             ms, k = ctx.timer_read(0)
         # the build is in parts and delivers 18 MB of rows on the way (330 us of the host link)
         assert k == 1 and ms < 3 * alone + 0.4, (alone, ms)
+
+
+def test_a_captured_build_is_not_timed(gpu_required):
+    """An asynchronous build captured by the caller: neither the capture nor a replay counts, forty of them (the ring
+    of intervals holds 32) leave the capture valid, and the replays build what an eager call builds."""
+    import torch
+    print("case timers capture", flush=True)
+    evs = [synth.make_event(n, cfg=37, event=i, noise=0.1) for i, n in enumerate((700, 300))]
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), abi.Context(abi.config_from_geometry(synth.Geometry(), max_cands=2)) as ctx:
+        hs = ctx.load_events([abi.EventArrays.from_synth(e) for e in evs])
+        want = ctx.build_batch(hs, [e.n_seeds for e in evs], flags=abi.BATCH_REINDEX)
+        ctx.build_batch(hs, flags=abi.BATCH_REINDEX | abi.BATCH_ASYNC)
+        ctx.sync()
+        ctx.timer_reset()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            for _ in range(40):
+                ctx.build_batch(hs, flags=abi.BATCH_REINDEX | abi.BATCH_ASYNC)
+        for _ in range(3):
+            graph.replay()
+            s.synchronize()
+            for h, e, w in zip(hs, evs, want):
+                got = ctx.fetch_tracks(h, e.n_seeds)
+                for k in ("par", "cov", "hits", "chi2", "status"):
+                    np.testing.assert_array_equal(got[k], w[k], err_msg=k)
+        assert [ctx.timer_read(k)[1] for k in range(3)] == [0, 0, 0]
+        ctx.build_batch(hs, flags=abi.BATCH_REINDEX | abi.BATCH_ASYNC)   # queued, then a replay behind it
+        graph.replay()
+        assert [ctx.timer_read(k)[1] for k in range(3)] == [1, 1, 0]
+        one = ctx.timer_read(0)[0]
+        ctx.build_batch(hs, flags=abi.BATCH_REINDEX | abi.BATCH_ASYNC)
+        assert ctx.timer_read(0)[0] < 3 * one    # a replay's time is 40 builds'
