@@ -379,6 +379,80 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     }
 }
 
+// The same for layers whose counters exceed a block's LDS, of events without
+// arrays for the bucketed build (their memory was not to be had): one range of
+// kIndexRange bins after the other, the layer's bins read twice for each.  The
+// counter of a range's last bin ends, after the placement, at the offset of
+// the next range's first.  Bound, as the form above, by one block's walk
+// through the layer's hits: ten layers of 68,000 hits 141 us on 65,536 bins (two
+// ranges), 304 on 262,144 (eight); the bucketed build 31 and 33, so an event
+// asks for its arrays first.
+constexpr int kIndexRange = (int)(kLayerBlockLds / sizeof(unsigned));
+
+__global__ void __launch_bounds__(1024) k_index_ranges(const Params P, const BatchArgs B, int only, const Stamp st)
+{
+    extern __shared__ unsigned s_cnt[];
+    __shared__ int s_wave[16];
+    stamp_start(st);
+    const int e = blockIdx.x / P.n_layers;
+    const int L = blockIdx.x - e * P.n_layers;
+    CEvent &E = event_desc(B.events, e);
+    if (only && E.part) return;               // the whole block: the bucketed build has this event
+    const int h0 = E.layer_off[L], n = E.layer_off[L + 1] - h0;
+    const LayerParam lp = P.layer[L];
+    const EvGrid g = ev_grid(P, E);
+    const int nb = g.bp * g.bz;
+    int *off = E.bin_off + L * bin_off_stride(nb);
+    const float4 *hits = E.hits + h0;
+    int *bin_of = E.bin_of + h0;
+    float4 *binned = E.binned + h0;
+    constexpr int kU = 4;
+    const int tid = threadIdx.x, stride = blockDim.x, step = kU * stride;
+    for (int base = tid; base < n; base += step) {
+        float4 v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = load_global(hits + min(base + u * stride, n - 1));
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (base + u * stride < n) store_global(bin_of + base + u * stride, bin_hit(P, lp, g, v[u]));
+    }
+    int first = 0;   // offset of the range's first bin in the layer
+    for (int lo = 0; lo < nb; lo += kIndexRange) {
+        const int nr = min(kIndexRange, nb - lo);
+        for (int i = tid; i < nr; i += stride) s_cnt[i] = 0u;
+        __syncthreads();
+        for (int base = tid; base < n; base += step) {   // a thread reads the bins it wrote itself
+            int b[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) b[u] = load_global(bin_of + (base + u * stride < n ? base + u * stride : base)) - lo;
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (base + u * stride < n && (unsigned)b[u] < (unsigned)nr) atomicAdd(&s_cnt[b[u]], 1u);
+        }
+        __syncthreads();
+        lds_scan_counts<false, 32>(s_cnt, nr, first, s_wave, off + lo, h0);   // ends on a barrier
+        for (int base = tid; base < n; base += step) {
+            int b[kU];
+            float4 v[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int i = base + u * stride < n ? base + u * stride : base;
+                b[u] = load_global(bin_of + i) - lo;
+                v[u] = load_global(hits + i);
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (base + u * stride < n && (unsigned)b[u] < (unsigned)nr)
+                    store_global(binned + atomicAdd(&s_cnt[b[u]], 1u),
+                                 make_float4(v[u].x, v[u].y, v[u].z, __int_as_float(base + u * stride)));
+        }
+        __syncthreads();
+        first = (int)s_cnt[nr - 1];
+        __syncthreads();
+    }
+    if (tid == 0) store_global(off + nb, h0 + n);
+}
+
 // Hit index of layers that each get many blocks, in three launches.  First
 // (k_index_hist) every chunk of a layer's hits is binned and its hits per
 // bucket of bins counted in LDS; then (k_index_part) each chunk takes its place
@@ -2067,7 +2141,8 @@ static hipError_t launch_index_layer(const Params &p, const BatchArgs &b, const 
 {
     const unsigned blocks = (unsigned)(b.n_events * p.n_layers);
     const size_t lds = layer_block_lds(x.layer_hits, x.bins);
-    if (x.layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, lds, s>>>(p, b, only, st);
+    if (!layer_block_fits(x.layer_hits, x.bins)) k_index_ranges<<<blocks, 1024, kLayerBlockLds, s>>>(p, b, only, st);
+    else if (x.layer_hits <= 0xFFFF) k_index_layer<true><<<blocks, 1024, lds, s>>>(p, b, only, st);
     else k_index_layer<false><<<blocks, 1024, lds, s>>>(p, b, only, st);
     return hipGetLastError();
 }

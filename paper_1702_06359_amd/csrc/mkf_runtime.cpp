@@ -50,7 +50,10 @@ void *CtxHeap::alloc(size_t bytes)
     if (bytes == 0) bytes = 256;
     if (ctx->has_alloc) return ctx->alloc.alloc(bytes, (void *)ctx->stream, ctx->alloc.user);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();   // not left for the next launch to report
+        return nullptr;
+    }
     return p;
 }
 
@@ -153,17 +156,14 @@ size_t carve_data(const EventShape &s, void *base, DevEvent *v, DevEvent **dev_v
     return c.off;
 }
 
-// Bytes of the working arrays of the bucketed index build (k_index_hist ff.);
-// 0, none, for an event that the one-block-per-layer build can index too (its
-// counters fit a block's LDS) when they exceed `allowance`.
-size_t index_work_bytes(const EventShape &s, int nb, size_t allowance, int *chunk, int *chunks)
+// Bytes of the working arrays of the bucketed index build (k_index_hist ff.).
+size_t index_work_bytes(const EventShape &s, int *chunk, int *chunks)
 {
     const int most = max_layer_hits(s);
     *chunk = idx_chunk_of(most);
     *chunks = (most + *chunk - 1) / *chunk;
-    const size_t need = (sizeof(float4) + sizeof(int)) * (size_t)s.n_hits() +
-                        sizeof(int) * (size_t)s.n_layers * ((size_t)*chunks * kBuckets + kBuckets + 1) + 4 * 256;
-    return need <= allowance || !layer_block_fits(most, nb) ? need : 0;
+    return (sizeof(float4) + sizeof(int)) * (size_t)s.n_hits() +
+           sizeof(int) * (size_t)s.n_layers * ((size_t)*chunks * kBuckets + kBuckets + 1) + 4 * 256;
 }
 
 // What the budget of a served event allows it beyond its inputs, FP32 result rows, binned
@@ -175,14 +175,25 @@ size_t index_allowance(const EventShape &s, int nb)
     return sizeof(int) * ((27 + 26) * (size_t)s.n_seeds + (size_t)s.n_hits() + (size_t)s.n_layers * nb);
 }
 
-size_t carve_index(const EventShape &s, int nb, bool served, void *base, DevEvent *v)
+// Whether an event asks for those arrays: one loaded for itself always, a
+// served one where its budget covers them or its layers' counters exceed a
+// block's LDS (the one-block-per-layer build then takes several times as
+// long).  Where the memory is not to be had it does without.
+bool wants_index_work(const EventShape &s, int nb, bool served)
+{
+    int chunk, chunks;
+    return !served || index_work_bytes(s, &chunk, &chunks) <= index_allowance(s, nb) ||
+           !layer_block_fits(max_layer_hits(s), nb);
+}
+
+size_t carve_index(const EventShape &s, int nb, bool work, void *base, DevEvent *v)
 {
     Carver c(base);
     const size_t nl = (size_t)s.n_layers, n = (size_t)s.n_hits();
     v->bin_off = c.take<int>(nl * bin_off_stride(nb));
     v->part = nullptr;
-    const size_t allow = served ? index_allowance(s, nb) : SIZE_MAX;
-    if (index_work_bytes(s, nb, allow, &v->idx_chunk, &v->idx_chunks)) {
+    if (work) {
+        index_work_bytes(s, &v->idx_chunk, &v->idx_chunks);
         v->bucket_shift = bucket_shift_of(nb);
         v->part = c.take<float4>(n);
         v->part_bin = c.take<int>(n);
@@ -630,10 +641,8 @@ size_t event_input_bytes(const EventShape &s)
 
 size_t event_budget_bytes(const EventShape &s, int nb)
 {
-    int chunk, chunks;
-    const size_t allow = index_allowance(s, nb), work = index_work_bytes(s, nb, allow, &chunk, &chunks);
     const size_t off = sizeof(int) * (size_t)s.n_layers * bin_off_stride(nb);
-    return round_up_256(event_data_bytes(s)) + round_up_256(off) + round_up_256(std::max(allow, work));
+    return round_up_256(event_data_bytes(s)) + round_up_256(off) + round_up_256(index_allowance(s, nb));
 }
 
 size_t batch_scratch_bytes(int n)
@@ -917,14 +926,20 @@ mkf_status ensure_index_grid(mkf_ctx *ctx, EventRec *rec, int bp, int bz, bool *
     const int k = event_grid_shift(max_layer_hits(rec->shape), bp, bz);
     const int nb = (bp >> k) * (bz >> k);
     const bool served = rec->heap != &ctx->heap;   // in the budget's slab
+    bool work = wants_index_work(rec->shape, nb, served);
     DevEvent sized{};
-    const size_t bytes = carve_index(rec->shape, nb, served, nullptr, &sized);
+    size_t bytes = carve_index(rec->shape, nb, work, nullptr, &sized);
     rec->index = rec->heap->alloc(bytes);
+    if (!rec->index && work) {
+        work = false;
+        bytes = carve_index(rec->shape, nb, work, nullptr, &sized);
+        rec->index = rec->heap->alloc(bytes);
+    }
     if (!rec->index) {
         rec->index_bins_phi = rec->index_bins_z = 0;
         return fail(MKF_E_NOMEM, "hit index: %zu bytes", bytes);
     }
-    carve_index(rec->shape, nb, served, rec->index, &rec->view);
+    carve_index(rec->shape, nb, work, rec->index, &rec->view);
     rec->view.grid_k = k;
     rec->index_bins_phi = bp;
     rec->index_bins_z = bz;
