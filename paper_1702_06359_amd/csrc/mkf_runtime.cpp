@@ -1826,14 +1826,21 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
         if (rec->plain) MKF_HIP(hipStreamSynchronize(ctx->stream));
         drop_plain_graph(rec);
         rec->heap->release(rec->plain);
-        const int slots = plain_slots(rec->shape.n_seeds, spi);
-        const size_t bytes = carve_plain(rec->shape, slots, nullptr, &rec->view);
-        rec->plain = rec->heap->alloc(bytes);
-        if (!rec->plain) {
-            rec->plain_G = 0;
-            return fail(MKF_E_NOMEM, "builder state: %zu bytes", bytes);
+        rec->plain = nullptr;
+        rec->plain_G = 0;
+        // fewer seeds per wavefront take more slots: where the memory for those
+        // is not to be had, full wavefronts
+        size_t bytes = 0;
+        for (int spw : {spi, kWave / G}) {
+            const int slots = plain_slots(rec->shape.n_seeds, spw);
+            bytes = carve_plain(rec->shape, slots, nullptr, &rec->view);
+            rec->plain = rec->heap->alloc(bytes);
+            if (!rec->plain) continue;
+            carve_plain(rec->shape, slots, rec->plain, &rec->view);
+            rec->plain_spw = spw;
+            break;
         }
-        carve_plain(rec->shape, slots, rec->plain, &rec->view);
+        if (!rec->plain) return fail(MKF_E_NOMEM, "builder state: %zu bytes", bytes);
         rec->plain_G = G;
         if ((st = upload_view(rec, ctx->stream)) != MKF_OK) return st;
     }
@@ -1845,7 +1852,7 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
             MKF_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
             hipError_t cap = hipSuccess;
             for (int L = rec->shape.n_seed_layers; L < rec->shape.n_layers && cap == hipSuccess; ++L)
-                cap = launch_build_layer(ctx->params, rec->dev_view, rec->view, L, G, spi, wpb, false, ctx->stream);
+                cap = launch_build_layer(ctx->params, rec->dev_view, rec->view, L, G, rec->plain_spw, wpb, false, ctx->stream);
             hipError_t end = hipStreamEndCapture(ctx->stream, &graph);
             if (cap != hipSuccess || end != hipSuccess) {
                 if (graph) (void)hipGraphDestroy(graph);

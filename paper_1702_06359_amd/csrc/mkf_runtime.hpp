@@ -88,7 +88,7 @@ struct EventRec {
     void *beam = nullptr;          // every rank of the final beam (allocated on first request)
     DevEvent beam_view{};          // its arrays (only the beam_* members are set)
     int index_bins_phi = 0, index_bins_z = 0;   // grid the index was built for (0 = none)
-    int plain_G = 0;
+    int plain_G = 0, plain_spw = 0;   // its lanes per seed and seeds per wavefront
     DevEvent view{};               // host copy of the device descriptor
     DevEvent *dev_view = nullptr;  // device copy (inside `data`)
     hipGraphExec_t plain_graph = nullptr;

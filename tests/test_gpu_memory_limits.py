@@ -108,6 +108,38 @@ def test_events_with_and_without_working_arrays_in_one_batch(gpu_required, monke
                 np.testing.assert_array_equal(a[k], b[k], err_msg=k)
 
 
+@pytest.mark.parametrize("cands", [1, 6])
+def test_the_per_event_builder_in_the_state_of_full_wavefronts(gpu_required, monkeypatch, cands):
+    """A small event spreads its seeds over more wavefronts, of 64 slots each: with room for the slots of full ones
+    alone (64 / lanes seeds a wavefront, 4 (31 + 1 + 1 + layers) bytes a slot) it is built in those; with less,
+    refused, and built once there is room."""
+    print("case builder memory", cands, flush=True)
+    n, lanes = 2001, cands
+    ev = synth.make_event(n, cfg=41, event=1, noise=0.2)
+    cfg = abi.config_from_geometry(ev.geometry, max_cands=cands)
+    memory = Capped()
+    with context(cfg, memory, monkeypatch) as c:
+        h = c.load_event(abi.EventArrays.from_synth(ev))
+        want = c.build_batch([h], [n])[0]
+        slots = -(-n // (64 // lanes)) * 64
+        state = 4 * (31 + 1 + 1 + 10) * slots
+        held = sum(memory.held.values())
+        memory.cap = held + state - 4096
+        with pytest.raises(abi.MkfError) as err:
+            c.build(h, n)
+        assert err.value.status == abi.E_NOMEM
+        for room in (2048, 64 * state):
+            memory.cap = held + state + room
+            for _ in range(2):
+                got = c.build(h, n)
+                for k in FIELDS:
+                    np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+            c.set_tuning(lanes_per_seed=8)      # the state is laid out anew
+            memory.cap = None
+            c.build(h, n)
+            c.set_tuning(lanes_per_seed=lanes)
+
+
 def _r(n):
     return (n + 255) & ~255
 
