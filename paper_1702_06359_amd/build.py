@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libmkf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["mkf_kernels.hip", "mkf_runtime.cpp", "mkf_serve.cpp", "mkf_pack.cpp"]
+SOURCES = ["mkf_kernels.hip", "mkf_runtime.cpp", "mkf_serve.cpp", "mkf_parts.cpp", "mkf_pack.cpp"]
 HEADERS = ["mkf_internal.hpp", "mkf_device.hpp", "mkf_runtime.hpp", "mkf_pack.hpp"]
 
 FLAGS = [

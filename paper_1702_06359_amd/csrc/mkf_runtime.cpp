@@ -1221,7 +1221,7 @@ class Delivery {
     long long total_rows() const { return total_; }
     // us per row on its way out: bytes over the host link, or copied out of
     // the staging
-    double us_per_row() const { return total_ ? (link_bytes_ / 55e3 + staged_ / 28e3) / (double)total_ : 0.0; }
+    double us_per_row() const { return total_ ? (link_bytes_ / kLinkBytesPerUs + staged_ / kCopyBytesPerUs) / (double)total_ : 0.0; }
 
     mkf_status finish()
     {
@@ -1400,79 +1400,6 @@ class Delivery {
     int cur_ = -1, n_slots_ = 0;
     bool begun_ = false, finished_ = false;
 };
-
-// How a batch whose rows go to the host is built: in parts (ends, in rows),
-// each part's rows delivered by the launch that builds the next, so that the
-// time is that of the longer of the two plus the first part's build and the
-// last one's delivery.  Parts end at blocks of kSeedBlock rows.  Chosen among
-// one part and sequences that start with a fraction of the rows and grow (for
-// rows that take longer to deliver than to build) or shrink, by the time that
-// a model of the launches gives, when it is at least 8 % shorter than that of
-// one part.  The model: a build takes `t0` (a wavefront's way through the
-// layers) plus `row` a seed, both in proportion to 0.45 + 0.55 of the fullest
-// layer's hits over 22,000, and 8/7 of it beside a delivery; a delivery takes
-// its bytes, a launch 4 us.  Measured with 6 candidates (us): thin cylinders
-// of 22,000 hits 10,240 seeds 50, 200,000 328, of 65,000 hits 10,240 seeds
-// 102, 50,000 213; disks of 11,000 hits 20,000 seeds 82, 40,000 104; deep
-// layers of 5,500 hits 20,000 seeds 86, of 22,000 hits 80,000 428.
-static std::vector<long long> plan_parts(const std::vector<EventLoad> &loads, const Params &P, double us_per_row)
-{
-    std::vector<long long> block;   // ends of the blocks
-    long long rows = 0;
-    double hits = 0.0;
-    for (const EventLoad &l : loads) {
-        for (int b = kSeedBlock; b < l.seeds; b += kSeedBlock) block.push_back(rows + b);
-        rows += l.seeds;
-        hits += (double)l.seeds * l.layer_hits;
-        if (l.seeds > 0) block.push_back(rows);
-    }
-    std::vector<long long> best{rows};
-    if (rows < 2 * kSeedBlock || us_per_row <= 0.0) return best;
-    const double dense = 0.45 + 0.55 * hits / (double)rows / 22000.0;
-    const double t0 = dense * (P.geo & 2 ? 58.0 : P.geo & 1 ? 55.0 : 33.0);
-    const double row = dense * (1.0 + P.max_cands) / 7.0 * (P.geo & 2 ? 4.6e-3 : P.geo & 1 ? 2.2e-3 : 1.48e-3);
-    auto time_of = [&](const std::vector<long long> &ends) {
-        double t = 0.0, out = 0.0;
-        long long at = 0;
-        for (long long e : ends) {
-            t += 4.0 + std::max((t0 + row * (double)(e - at)) * (at ? 8.0 / 7.0 : 1.0), out);
-            out = us_per_row * (double)(e - at);
-            at = e;
-        }
-        return t + 4.0 + out;
-    };
-    double best_t = 0.92 * time_of(best);
-    for (double first : {0.05, 0.1, 0.2, 0.33, 0.5, 0.62, 0.75})
-        for (double growth : {0.5, 1.0, 2.0, 3.0}) {
-            std::vector<long long> ends;
-            double want = first * (double)rows, size = want;
-            for (size_t k = 0; k < block.size() && (int)ends.size() + 1 < kBuildParts; ++k) {
-                if ((double)block[k] < want && k + 1 < block.size()) continue;
-                ends.push_back(block[k]);
-                size = std::max(size * growth, (double)kSeedBlock);
-                want = (double)block[k] + size;
-            }
-            if (ends.empty() || ends.back() < rows) ends.push_back(rows);
-            const double t = time_of(ends);
-            if (t < best_t) {
-                best_t = t;
-                best = ends;
-            }
-        }
-    return best;
-}
-
-// Work items of the first `rows` rows (whole blocks or events) of a batch.
-static int items_before(const std::vector<EventLoad> &loads, long long rows, int spi)
-{
-    long long items = 0;
-    for (const EventLoad &l : loads) {
-        const long long m = std::min<long long>(l.seeds, rows);
-        items += (m + spi - 1) / spi;
-        rows -= m;
-    }
-    return (int)items;
-}
 
 mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args, uint32_t flags,
                         bool timed, hipStream_t s, Delivery *d, const std::vector<EventLoad> &loads)

@@ -251,6 +251,12 @@ struct EventLoad {
     int seeds;
     int layer_hits;   // of its fullest layer
 };
+// The rows each part of a batch ends at, and the work items before a row: see
+// their definitions.  Rows leave at the host link's rate, or at that of one
+// host thread copying them out of the staging.
+constexpr double kLinkBytesPerUs = 55e3, kCopyBytesPerUs = 28e3;
+std::vector<long long> plan_parts(const std::vector<EventLoad> &loads, const Params &P, double us_per_row);
+int items_before(const std::vector<EventLoad> &loads, long long rows, int spi);
 mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, const BatchArgs &args, uint32_t flags,
                         bool timed, hipStream_t s, Delivery *d = nullptr, const std::vector<EventLoad> &loads = {});
 // The fields of a result row (par, cov, chi2 in FP64, then hits, n_hits,
