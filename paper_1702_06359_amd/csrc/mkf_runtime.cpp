@@ -619,6 +619,17 @@ int pack_threads(size_t n_values, size_t per_thread)
     return (int)std::min<size_t>({(size_t)16, (size_t)hw, 1 + n_values / per_thread});
 }
 
+void touch_pages(const void *p, size_t bytes)
+{
+    constexpr size_t kPage = 4096, kTask = 16 * kPage;   // 22 us; a thread takes 30 to 50 us to wake
+    const volatile char *at = static_cast<const volatile char *>(p);
+    const size_t tasks = (bytes + kTask - 1) / kTask;
+    const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
+    run_tasks((int)tasks, (int)std::min<size_t>({(size_t)16, (size_t)hw, (tasks + 1) / 2}), [=](int t) {
+        for (size_t i = t * kTask; i < std::min(bytes, (t + 1) * kTask); i += kPage) (void)at[i];
+    });
+}
+
 // the hits, at the front of the inputs, up to where the seeds begin
 size_t event_hit_bytes(const EventShape &s) { return round_up_256(sizeof(float4) * (size_t)s.n_hits()); }
 

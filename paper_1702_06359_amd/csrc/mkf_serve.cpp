@@ -30,9 +30,11 @@ size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 // Page-locked staging, inputs and results apart: an input buffer so stays in
 // the cache of the threads that pack into it instead of coming back from the
 // one that copies results out (one submit of 10,900 seeds: 151 against 319 us).
-// Taken from two slabs made at configuration (page-locking a buffer as it is
-// first needed took most of a submit: 16 submits 7.5-10 ms); when a slab is
-// full, from buffers reused by power-of-two size class.
+// Taken from two slabs made at configuration; when a slab is full, from buffers
+// reused by power-of-two size class.  The first burst of a new server goes
+// through pages of its slabs that the host has never touched: the first of
+// them are touched at configuration, the others by several threads as they are
+// first handed out (touch_pages).
 class PinnedPool {
   public:
     enum Use { kInput, kResult };
@@ -45,13 +47,19 @@ class PinnedPool {
             base_ = nullptr;
             return;
         }
-        for (int u = 0; u < 2; ++u) slab_[u] = std::make_unique<SlabHeap>(base_ + u * bytes, bytes);
+        for (Use u : {kInput, kResult}) {
+            slab_[u] = std::make_unique<SlabHeap>(base_ + u * bytes, bytes);
+            touch_to(u, kTouchFirst);
+        }
     }
     void *get(size_t bytes, Use use, size_t *cls)
     {
         *cls = 0;   // from the slab
         if (slab_[use])
-            if (void *p = slab_[use]->alloc(bytes)) return p;
+            if (void *p = slab_[use]->alloc(bytes)) {
+                touch_to(use, static_cast<char *>(p) - slab_base(use) + bytes);
+                return p;
+            }
         size_t c = 4096;
         while (c < bytes) c <<= 1;
         *cls = c;
@@ -65,7 +73,10 @@ class PinnedPool {
             }
         }
         void *p = nullptr;
-        if (hipHostMalloc(&p, c, hipHostMallocDefault) != hipSuccess) return nullptr;
+        if (hipHostMalloc(&p, c, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();   // not left for the next launch to report
+            return nullptr;
+        }
         return p;
     }
     void put(void *p, Use use, size_t cls)
@@ -87,8 +98,26 @@ class PinnedPool {
     }
 
   private:
+    // a few events of 1,000 tracks; and the steps of what follows
+    static constexpr size_t kTouchFirst = size_t(2) << 20, kTouchStep = size_t(256) << 10;
+
+    char *slab_base(Use use) const { return base_ + use * slab_[use]->capacity(); }
+
+    // every page of the slab below `end` touched
+    void touch_to(Use use, size_t end)
+    {
+        const size_t to = std::min(slab_[use]->capacity(), (end + kTouchStep - 1) / kTouchStep * kTouchStep);
+        size_t from = touched_[use].load();
+        while (from < to)
+            if (touched_[use].compare_exchange_weak(from, to)) {
+                touch_pages(slab_base(use) + from, to - from);
+                return;
+            }
+    }
+
     std::mutex mu_;
     char *base_ = nullptr;
+    std::atomic<size_t> touched_[2] = {};
     std::unique_ptr<SlabHeap> slab_[2];
     std::map<size_t, std::vector<void *>> free_[2];
 };
