@@ -385,9 +385,10 @@ mkf_status mkf_autotune(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tun
 /* Configure serving: device-memory budget in bytes (reserved at once, a
  * slab that admitted events are placed in), events in flight (submitted and
  * not finished), events per batched build (0 = all that are waiting).  Also
- * allocates, outside the budget, the batch descriptors of each stream and
- * page-locked staging for inputs and results (up to 64 MiB, no more than the
- * budget).
+ * allocates, outside the budget, the batch descriptors of each stream; submits
+ * take page-locked staging for inputs and results as they need it (in slabs of
+ * up to 64 MiB together, no more than the budget, kept until the next
+ * configuration).
  * Errors: MKF_E_INVALID, MKF_E_NOMEM (the budget cannot be reserved),
  * MKF_E_STATE (tickets of a previous configuration still in flight),
  * MKF_E_DEVICE. */

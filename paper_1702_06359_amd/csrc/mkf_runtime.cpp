@@ -1199,9 +1199,21 @@ class Delivery {
         n_recs_ = outs ? n : 0;
         outs_ = outs;
     }
-    bool expects_rows() const { return n_recs_ > 0 || !rows_.empty(); }
+    // whether adding and preparing the rows of n events may take longer than the
+    // shortest phase (an index, 9 us): the arrays of an event take 0.6 us to
+    // look up
+    bool slow_to_prepare(size_t rows, int n) const
+    {
+        return n > 8 || (!fixed_ && n && out_pin_bytes(rows, n, args_.n_layers) > ctx_->load_pin_bytes);
+    }
+    bool slow_to_prepare() const
+    {
+        size_t rows = 0;
+        for (int i = 0; i < n_recs_; ++i) rows += (size_t)recs_[i]->shape.n_seeds;
+        return slow_to_prepare(rows, n_recs_);
+    }
 
-    // What takes the host long - looking up the arrays of many events, growing
+    // What may take the host long - looking up the arrays of many events, growing
     // the staging - before the launch whose end the delivery's will stamp, so
     // that the phase's time holds none of it.  Nothing is added afterwards.
     mkf_status prepare()
@@ -1422,9 +1434,9 @@ mkf_status run_pipeline(mkf_ctx *ctx, const Params &P, const mkf_tuning &t, cons
         MKF_HIP(launch_index(P, args, s, timed ? take_stamp(ctx) : Stamp{}));
     }
     if (t.persistent) MKF_HIP(launch_fill_i32(reinterpret_cast<int *>(args.queue), 0, 1, s));
-    // one index build of the batch; with rows to deliver the host has work to do
-    // before the next launch, so the index's end gets a stamp of its own
-    if (timed && reindex && !(d && d->expects_rows())) {
+    // one index build of the batch, its end stamped by the build's launch, or by
+    // a launch of its own (1.5 us) where the host may be late with that
+    if (timed && reindex && !(d && d->slow_to_prepare())) {
         timer_switch(ctx, 1, 0, s, 1);
     } else if (timed) {
         if (reindex) timer_end(ctx, 1, s, 1);
@@ -1804,12 +1816,16 @@ mkf_status mkf_build(mkf_ctx *ctx, int32_t handle, mkf_tracks *out)
             rec->plain_graph_wpb = wpb;
         }
         Delivery d(ctx);
-        if (out) d.add(build_rows(rec, *out));
-        if ((st = d.prepare()) != MKF_OK) return st;
+        const bool first = out && d.slow_to_prepare((size_t)rec->shape.n_seeds, 1);
+        if (first) {
+            d.add(build_rows(rec, *out));
+            if ((st = d.prepare()) != MKF_OK) return st;
+        }
         timer_begin(ctx, 0, ctx->stream);
         stamp_now(ctx);
         MKF_HIP(hipGraphLaunch(rec->plain_graph, ctx->stream));
         timer_end(ctx, 0, ctx->stream, n_launch);
+        if (out && !first) d.add(build_rows(rec, *out));
         if ((st = d.finish()) != MKF_OK) return st;
     } else {
         MKF_HIP(hipStreamSynchronize(ctx->stream));
@@ -2165,12 +2181,11 @@ mkf_status mkf_fit(mkf_ctx *ctx, int32_t handle, int32_t n_tracks, const double 
     if ((st = stage_batch(ctx, one, ctx->batch_dev, ctx->batch_host, 64, &args, s)) != MKF_OK) return cleanup(st);
     {
         Delivery d(ctx);
-        if (out) d.add(OutRows{v.fit_rec, v.track_hits, n_tracks, *out});
-        if ((st = d.prepare()) != MKF_OK) return cleanup(st);
         timer_begin(ctx, 2, s);
         const hipError_t e = launch_fit(ctx->params, args, s, take_stamp(ctx));
         timer_end(ctx, 2, s, 1);
         if (e != hipSuccess) return cleanup(fail(MKF_E_DEVICE, "fit launch: %s", hipGetErrorString(e)));
+        if (out) d.add(OutRows{v.fit_rec, v.track_hits, n_tracks, *out});   // (its staging is there)
         if ((st = d.finish()) != MKF_OK) return cleanup(st);
     }
     timers_collect(ctx, false);   // all has run

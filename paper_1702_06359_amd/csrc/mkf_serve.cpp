@@ -30,32 +30,20 @@ size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 // Page-locked staging, inputs and results apart: an input buffer so stays in
 // the cache of the threads that pack into it instead of coming back from the
 // one that copies results out (one submit of 10,900 seeds: 151 against 319 us).
-// Taken from two slabs made at configuration; when a slab is full, from buffers
-// reused by power-of-two size class.  The first burst of a new server goes
-// through pages of its slabs that the host has never touched: the first of
-// them are touched at configuration, the others by several threads as they are
-// first handed out (touch_pages).
+// Small buffers are reused by power-of-two size class: the runtime has them at
+// hand (two 45 us).  Larger ones come from two slabs made when the first is
+// asked for (64 MB: 0.8 ms), whose pages the host has never touched before:
+// several threads touch them as they are first handed out (touch_pages).  When
+// a slab is full, the classes serve large buffers too.
 class PinnedPool {
   public:
     enum Use { kInput, kResult };
 
-    // slabs of `bytes` each; without them where they cannot be had
-    void reserve(size_t bytes)
-    {
-        if (hipHostMalloc(reinterpret_cast<void **>(&base_), 2 * bytes, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            base_ = nullptr;
-            return;
-        }
-        for (Use u : {kInput, kResult}) {
-            slab_[u] = std::make_unique<SlabHeap>(base_ + u * bytes, bytes);
-            touch_to(u, kTouchFirst);
-        }
-    }
+    void limit(size_t bytes) { slab_bytes_ = bytes; }   // of each slab
     void *get(size_t bytes, Use use, size_t *cls)
     {
         *cls = 0;   // from the slab
-        if (slab_[use])
+        if (bytes > kSmall && reserve())
             if (void *p = slab_[use]->alloc(bytes)) {
                 touch_to(use, static_cast<char *>(p) - slab_base(use) + bytes);
                 return p;
@@ -98,15 +86,30 @@ class PinnedPool {
     }
 
   private:
-    // a few events of 1,000 tracks; and the steps of what follows
-    static constexpr size_t kTouchFirst = size_t(2) << 20, kTouchStep = size_t(256) << 10;
+    static constexpr size_t kSmall = size_t(512) << 10;
+    static constexpr size_t kTouchStep = size_t(256) << 10;
 
-    char *slab_base(Use use) const { return base_ + use * slab_[use]->capacity(); }
+    // the slabs, made once; false where they cannot be had
+    bool reserve()
+    {
+        std::lock_guard<std::mutex> lk(slab_mu_);
+        if (asked_) return base_ != nullptr;
+        asked_ = true;
+        if (hipHostMalloc(reinterpret_cast<void **>(&base_), 2 * slab_bytes_, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            base_ = nullptr;
+            return false;
+        }
+        for (int u = 0; u < 2; ++u) slab_[u] = std::make_unique<SlabHeap>(base_ + u * slab_bytes_, slab_bytes_);
+        return true;
+    }
+
+    char *slab_base(Use use) const { return base_ + use * slab_bytes_; }
 
     // every page of the slab below `end` touched
     void touch_to(Use use, size_t end)
     {
-        const size_t to = std::min(slab_[use]->capacity(), (end + kTouchStep - 1) / kTouchStep * kTouchStep);
+        const size_t to = std::min(slab_bytes_, (end + kTouchStep - 1) / kTouchStep * kTouchStep);
         size_t from = touched_[use].load();
         while (from < to)
             if (touched_[use].compare_exchange_weak(from, to)) {
@@ -115,7 +118,9 @@ class PinnedPool {
             }
     }
 
-    std::mutex mu_;
+    std::mutex mu_, slab_mu_;
+    size_t slab_bytes_ = 0;
+    bool asked_ = false;
     char *base_ = nullptr;
     std::atomic<size_t> touched_[2] = {};
     std::unique_ptr<SlabHeap> slab_[2];
@@ -415,7 +420,7 @@ mkf_status mkf_serve_config(mkf_ctx *ctx, uint64_t hbm_budget_bytes, int32_t max
         }
     }
     // as much of each as the budget could hold in flight, up to 32 MiB
-    sv->pinned.reserve(std::min<size_t>(hbm_budget_bytes / 2 & ~uint64_t(4095), size_t(32) << 20));
+    sv->pinned.limit(std::min<size_t>(hbm_budget_bytes / 2 & ~uint64_t(4095), size_t(32) << 20));
     ctx->server = std::move(sv);
     Server *raw = ctx->server.get();
     raw->thr = std::thread([raw] { raw->loop(); });

@@ -37,8 +37,8 @@ def _outs(evs):
 
 def test_a_first_burst_takes_little_longer_than_the_next(gpu_required):
     """8 events, 60,000 tracks, 39 MB through the staging: the next burst takes about 2 ms, the pages of the first 13
-    ms more by one thread, 1 ms by sixteen.  The best of five servers, so that a busy host does not decide; all of
-    them stay open, so that each has memory of its own."""
+    ms more by two threads in turn, 1 ms by sixteen, and the slabs 1 ms to make.  The best of five servers, so that a
+    busy host does not decide; all of them stay open, so that each has memory of its own."""
     evs = [synth.make_event(n, cfg=44, event=i, noise=0.2) for i, n in enumerate((3000, 5000, 6000, 7000, 8000, 9000,
                                                                                  10000, 12000))]
     inputs, outs = [abi.EventArrays.from_synth(e) for e in evs], _outs(evs)
@@ -57,11 +57,11 @@ def test_a_first_burst_takes_little_longer_than_the_next(gpu_required):
         for c in open_:
             c.close()
     print("first", [int(1e6 * t) for t in first], "next", [int(1e6 * t) for t in nxt], flush=True)
-    assert min(first) < 3 * np.median(nxt)
+    assert min(first) < 3.5 * np.median(nxt)
 
 
 def test_concurrent_submits_into_new_pages_keep_their_inputs(gpu_required):
-    evs = [synth.make_event(300 + 37 * i, cfg=45, event=i, noise=0.2) for i in range(24)]
+    evs = [synth.make_event(1900 + 37 * i, cfg=45, event=i, noise=0.2) for i in range(24)]
     inputs = [abi.EventArrays.from_synth(e) for e in evs]
     with abi.Context(abi.config_from_geometry(synth.Geometry(), max_cands=2)) as c:
         hs = c.load_events(inputs)
