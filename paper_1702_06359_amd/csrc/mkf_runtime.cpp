@@ -1200,11 +1200,12 @@ class Delivery {
         outs_ = outs;
     }
     // whether adding and preparing the rows of n events may take longer than the
-    // shortest phase (an index, 9 us): the arrays of an event take 0.6 us to
-    // look up
+    // shortest phase, an index of 9 us behind a launch of 5: the arrays of an
+    // event take 0.6 us to look up.  (Where it may, a stamp in front or the
+    // look-ups before the launch cost a call of 20 small events 2 of 128 us.)
     bool slow_to_prepare(size_t rows, int n) const
     {
-        return n > 8 || (!fixed_ && n && out_pin_bytes(rows, n, args_.n_layers) > ctx_->load_pin_bytes);
+        return n > 16 || (!fixed_ && n && out_pin_bytes(rows, n, args_.n_layers) > ctx_->load_pin_bytes);
     }
     bool slow_to_prepare() const
     {
@@ -2100,12 +2101,21 @@ mkf_status mkf_fit_batch(mkf_ctx *ctx, const int32_t *handles, int32_t n, mkf_tr
     if ((st = stage_batch(ctx, recs, ctx->batch_dev, ctx->batch_host, 64, &args, ctx->stream)) != MKF_OK)
         return st;
     Delivery d(ctx);
-    for (int i = 0; outs && i < n; ++i)
-        d.add(OutRows{recs[i]->view.fit_rec, recs[i]->view.track_hits, recs[i]->shape.n_tracks, outs[i]});
-    if ((st = d.prepare()) != MKF_OK) return st;
+    size_t rows = 0;
+    for (const EventRec *r : recs) rows += (size_t)r->shape.n_tracks;
+    auto add = [&] {
+        for (int i = 0; outs && i < n; ++i)
+            d.add(OutRows{recs[i]->view.fit_rec, recs[i]->view.track_hits, recs[i]->shape.n_tracks, outs[i]});
+    };
+    const bool first = outs && d.slow_to_prepare(rows, n);
+    if (first) {
+        add();
+        if ((st = d.prepare()) != MKF_OK) return st;
+    }
     timer_begin(ctx, 2, ctx->stream);
     MKF_HIP(launch_fit(ctx->params, args, ctx->stream, take_stamp(ctx)));
     timer_end(ctx, 2, ctx->stream, 1);
+    if (!first) add();
     if ((st = d.finish()) != MKF_OK) return st;
     timers_collect(ctx, false);   // all has run
     return MKF_OK;
