@@ -57,7 +57,7 @@ def test_a_first_burst_takes_little_longer_than_the_next(gpu_required):
         for c in open_:
             c.close()
     print("first", [int(1e6 * t) for t in first], "next", [int(1e6 * t) for t in nxt], flush=True)
-    # 2.4-2.8 on three boxes; 4.7-5.0 with the pages left to the two threads
+    # 2.4-2.8 on three machines; 4.7-5.0 with the pages left to the two threads
     assert min(first) < 3.75 * np.median(nxt)
 
 
